@@ -13,7 +13,10 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpsms.so")
 
-SOURCES = ["box_kernels.hip", "channel_kernels.hip", "channel_step_kernels.hip", "adjoint_kernels.hip", "api.cpp"]
+# (source, extra flags): box_kernels.hip in two parts, which compile side by side
+SOURCES = [("box_kernels.hip", ["-DPSMS_PART=64"]), ("box_kernels.hip", ["-DPSMS_PART=32"]),
+           ("channel_kernels.hip", []), ("channel_step_kernels.hip", []), ("adjoint_kernels.hip", []),
+           ("api.cpp", [])]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
@@ -33,9 +36,9 @@ FLAGS = [
 def build(verbose: bool = False) -> str:
     objs = []
     procs = []
-    for src in SOURCES:
-        obj = os.path.join(CSRC, os.path.splitext(src)[0] + ".o")
-        cmd = [HIPCC] + FLAGS + ["-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj]
+    for k, (src, extra) in enumerate(SOURCES):
+        obj = os.path.join(CSRC, "%s_%d.o" % (os.path.splitext(src)[0], k))
+        cmd = [HIPCC] + FLAGS + extra + ["-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)))

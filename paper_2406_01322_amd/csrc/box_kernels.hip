@@ -31,6 +31,13 @@
 #include "box_kernels.hpp"
 #include "fft_engine.hpp"
 
+// The build compiles this file twice, side by side: with PSMS_PART = 64 the FP64
+// instantiations and everything that is not a template, with PSMS_PART = 32 the
+// FP32 instantiations.
+#ifndef PSMS_PART
+#error "compile with -DPSMS_PART=64 and -DPSMS_PART=32"
+#endif
+
 namespace psms {
 
 template <typename T>
@@ -856,6 +863,7 @@ __global__ void k_pressure_band(const cpx<T>* __restrict__ t6, BoxGeom g, cpx<do
   }
 }
 
+#if PSMS_PART == 64
 // Leray projection of the compact velocity [3][M] in place (k = 0 -> 0).
 __global__ void k_project(cpx<double>* __restrict__ u, BoxGeom g) {
   for (long long id = blockIdx.x * (long long)blockDim.x + threadIdx.x; id < g.M;
@@ -881,6 +889,8 @@ __global__ void k_project(cpx<double>* __restrict__ u, BoxGeom g) {
   }
 }
 
+#endif
+
 // Full half spectrum: optional 2/3 mask and i k_axis factor, scale.
 template <typename T>
 __global__ void k_spec_finish(const cpx<T>* __restrict__ in, cpx<T>* __restrict__ out, BoxGeom g, int nf,
@@ -904,6 +914,7 @@ __global__ void k_spec_finish(const cpx<T>* __restrict__ in, cpx<T>* __restrict_
   }
 }
 
+#if PSMS_PART == 64
 // Helmholtz (lap - lambda_f) f = g per mode: f = -g / (k^2 + lambda_f).
 __global__ void k_helmholtz_box(const cpx<double>* __restrict__ rhs, cpx<double>* __restrict__ out, BoxGeom g,
                                 int nf, double lam) {
@@ -1050,11 +1061,14 @@ __global__ void k_diag_final(const double* __restrict__ part, int nb, const cpx<
   }
 }
 
+#endif
+
 // ---------------------------------------------------------------------------
 // host-side launchers (dispatch on the transform length)
 // ---------------------------------------------------------------------------
 #define PSMS_FOR_EACH_N(X) X(8) X(12) X(16) X(24) X(32) X(48) X(64) X(96) X(128) X(192) X(256)
 
+#if PSMS_PART == 64
 bool supported_n(int n) {
   switch (n) {
 #define PSMS_CASE(NN) case NN:
@@ -1065,6 +1079,8 @@ bool supported_n(int n) {
       return false;
   }
 }
+
+#endif
 
 namespace {
 
@@ -1169,9 +1185,6 @@ hipError_t launch_xstage_rows(int n, const BoxDev* dev, const cpx<T>* tw, long l
   }
   return hipErrorInvalidValue;
 }
-template hipError_t launch_xstage_rows<float>(int, const BoxDev*, const cpx<float>*, long long, double, hipStream_t);
-template hipError_t launch_xstage_rows<double>(int, const BoxDev*, const cpx<double>*, long long, double,
-                                               hipStream_t);
 
 template <typename T>
 hipError_t launch_lines(int n, int dir, const cpx<T>* in, cpx<T>* out, const cpx<T>* tw, const LineArgs& a,
@@ -1225,10 +1238,13 @@ hipError_t launch_compact(const cpx<T>* full, cpx<T>* cmp, const BoxGeom& g, int
   k_compact<T><<<grid_for(g.M * nf), 256, 0, st>>>(full, cmp, g, nf);
   return hipGetLastError();
 }
+#if PSMS_PART == 64
 hipError_t launch_project(cpx<double>* u, const BoxGeom& g, hipStream_t st) {
   k_project<<<grid_for(g.M), 256, 0, st>>>(u, g);
   return hipGetLastError();
 }
+#endif
+
 template <typename T>
 hipError_t launch_band_to(const cpx<double>* a, cpx<T>* out, long long n, hipStream_t st) {
   k_band_to<T><<<grid_for(n), 256, 0, st>>>(a, out, n);
@@ -1244,11 +1260,6 @@ hipError_t launch_pressure_band(const cpx<T>* t6, const BoxGeom& g, cpx<double>*
   k_pressure_band<T><<<grid_for(g.M), 256, 0, st>>>(t6, g, p);
   return hipGetLastError();
 }
-template hipError_t launch_band_to<float>(const cpx<double>*, cpx<float>*, long long, hipStream_t);
-template hipError_t launch_cube<float>(float*, long long, hipStream_t);
-template hipError_t launch_cube<double>(double*, long long, hipStream_t);
-template hipError_t launch_pressure_band<float>(const cpx<float>*, const BoxGeom&, cpx<double>*, hipStream_t);
-template hipError_t launch_pressure_band<double>(const cpx<double>*, const BoxGeom&, cpx<double>*, hipStream_t);
 template <typename T>
 hipError_t launch_spec_finish(const cpx<T>* in, cpx<T>* out, const BoxGeom& g, int nf, int dealias, int axis,
                               double scale, hipStream_t st) {
@@ -1256,6 +1267,7 @@ hipError_t launch_spec_finish(const cpx<T>* in, cpx<T>* out, const BoxGeom& g, i
   k_spec_finish<T><<<grid_for(tot), 256, 0, st>>>(in, out, g, nf, dealias, axis, scale);
   return hipGetLastError();
 }
+#if PSMS_PART == 64
 hipError_t launch_helmholtz_box(const cpx<double>* rhs, cpx<double>* out, const BoxGeom& g, double lam,
                                 hipStream_t st) {
   const long long tot = (long long)g.n * g.n * (g.n / 2 + 1);
@@ -1291,23 +1303,26 @@ hipError_t launch_diag(const cpx<double>* state, const BoxGeom& g, double* part,
   return hipGetLastError();
 }
 
-template hipError_t launch_lines<double>(int, int, const cpx<double>*, cpx<double>*, const cpx<double>*,
-                                         const LineArgs&, int, hipStream_t);
-template hipError_t launch_lines<float>(int, int, const cpx<float>*, cpx<float>*, const cpx<float>*,
-                                        const LineArgs&, int, hipStream_t);
-template hipError_t launch_rows<double>(int, int, const void*, void*, const cpx<double>*, const RowArgs&, int,
-                                        hipStream_t);
-template hipError_t launch_rows<float>(int, int, const void*, void*, const cpx<float>*, const RowArgs&, int,
-                                       hipStream_t);
-template hipError_t launch_step_stage<double>(int, int, int, const BoxDev*, int, int, const cpx<double>*, int,
-                                              hipStream_t);
-template hipError_t launch_step_stage<float>(int, int, int, const BoxDev*, int, int, const cpx<float>*, int,
-                                             hipStream_t);
+#endif
+
+#if PSMS_PART == 64
+using PartT = double;
 template hipError_t launch_expand<double>(const cpx<double>*, cpx<double>*, const BoxGeom&, int, hipStream_t);
 template hipError_t launch_compact<double>(const cpx<double>*, cpx<double>*, const BoxGeom&, int, hipStream_t);
-template hipError_t launch_spec_finish<double>(const cpx<double>*, cpx<double>*, const BoxGeom&, int, int, int,
-                                               double, hipStream_t);
-template hipError_t launch_spec_finish<float>(const cpx<float>*, cpx<float>*, const BoxGeom&, int, int, int, double,
+#else
+using PartT = float;
+template hipError_t launch_band_to<float>(const cpx<double>*, cpx<float>*, long long, hipStream_t);
+#endif
+template hipError_t launch_xstage_rows<PartT>(int, const BoxDev*, const cpx<PartT>*, long long, double, hipStream_t);
+template hipError_t launch_cube<PartT>(PartT*, long long, hipStream_t);
+template hipError_t launch_pressure_band<PartT>(const cpx<PartT>*, const BoxGeom&, cpx<double>*, hipStream_t);
+template hipError_t launch_lines<PartT>(int, int, const cpx<PartT>*, cpx<PartT>*, const cpx<PartT>*, const LineArgs&,
+                                        int, hipStream_t);
+template hipError_t launch_rows<PartT>(int, int, const void*, void*, const cpx<PartT>*, const RowArgs&, int,
+                                       hipStream_t);
+template hipError_t launch_step_stage<PartT>(int, int, int, const BoxDev*, int, int, const cpx<PartT>*, int,
+                                             hipStream_t);
+template hipError_t launch_spec_finish<PartT>(const cpx<PartT>*, cpx<PartT>*, const BoxGeom&, int, int, int, double,
                                               hipStream_t);
 
 }  // namespace psms

@@ -1,0 +1,42 @@
+"""GPU parity of kernel paths chosen by size, at the sizes where each can go wrong."""
+import numpy as np
+import pytest
+
+from oracle import box
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+def _dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def _host(t):
+    torch.cuda.synchronize()
+    return t.cpu().numpy()
+
+
+# Every 3 * 2^m plan, whole half spectrum: one butterfly a thread (12, 24), partial
+# rounds of radix-4 (48, 192, twice in 192) and radix-8 butterflies (96).  Bars:
+# FP64 1e-13 of the maximum for each 16 points of a line; FP32 1e-6 rel-L2
+# (three passes of about log2(N) 2^-24 each).
+@pytest.mark.parametrize("n", [12, 24, 48, 96, 192])
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_radix_6_plans_transform_both_ways(n, precision):
+    from paper_2406_01322_amd.psms import Solver
+    rng = np.random.default_rng(n)
+    s = Solver(n, 100.0, 1.0, 0.05, 20.0, 1e-3, precision=precision)
+    real, cplx = (np.float64, np.complex128) if precision == "fp64" else (np.float32, np.complex64)
+    f = rng.standard_normal((n, n, n)).astype(real)
+    want = box.transform_forward(f.astype(np.float64))
+    got = _host(s.transform(+1, _dev(f), 0)).astype(np.complex128)
+    fh = want.astype(cplx)
+    back = _host(s.transform(-1, _dev(fh), 0)).astype(np.float64)
+    wback = box.transform_inverse(fh.astype(np.complex128))
+    for a, b in ((got, want), (back, wback)):
+        if precision == "fp64":
+            assert np.max(np.abs(a - b)) <= 1e-13 * max(1, n // 16) * np.max(np.abs(b))
+        else:
+            assert np.linalg.norm(a - b) <= 1e-6 * np.linalg.norm(b)

@@ -87,8 +87,8 @@ Layout make_layout(const psms_params& p) {
   L.diag = off; off = align256(off + 4 * kDiagBlocks * sizeof(double));
   L.diag_out = off; off = align256(off + 8 * sizeof(double));
   L.box = off; off = align256(off + sizeof(psms::BoxDev));
-  L.phys = off; off = align256(off + n * n * n * sizeof(double));   // CFL: one physical component
-  L.acc = off; off = align256(off + n * n * n * sizeof(double));    // CFL: sum_i |u_i| / dx
+  L.phys = off; off = align256(off + n * n * n * sizeof(double));   // CFL: u on the grid
+  L.acc = off; off = align256(off + n * n * n * sizeof(double));    // CFL: v on the grid
   L.m = 0;
   if (p.cube == 1) {
     const size_t m = size_t(pad_size(p.n));
@@ -343,30 +343,78 @@ hipError_t transform_fields(psms_ctx* c, int dir, int nf, const void* d_in, void
   ra.n_in = nh;
   ra.n_out = nh;
   ra.scale = 1.0;
+  // as many fields per launch as both scratch buffers hold (3 or 4: they are
+  // sized for the step's 6 and 8 pruned fields); the spectrum gets its own pass
+  // only if it is masked or multiplied by i k.  A chunk's input is read whole
+  // before its output is written, as d_in may be d_out.
+  const int chunk = int(std::min<size_t>(8, std::min(c->lay.bufa_bytes, c->lay.bufb_bytes) / (nfull * sizeof(cpx<T>))));
+  ly.in_fstride = ly.out_fstride = lz.in_fstride = lz.out_fstride = (long long)nfull;
+  ly.fmap = lz.fmap = 0x76543210u;
+  const bool finish = dealias || axis >= 0;
   hipError_t e;
-  for (int f = 0; f < nf; ++f) {
+  for (int f = 0; f < nf; f += chunk) {
+    const int k = std::min(chunk, nf - f);
     if (dir > 0) {
       const T* src = static_cast<const T*>(d_in) + f * nphys;
       cpx<T>* dst = static_cast<cpx<T>*>(d_out) + f * nfull;
       ra.n_in = n;
-      if ((e = psms::launch_rows<T>(n, -1, src, A, tw, ra, 1, c->stream)) != hipSuccess) return e;
-      if ((e = psms::launch_lines<T>(n, -1, A, B, tw, ly, 1, c->stream)) != hipSuccess) return e;
-      if ((e = psms::launch_lines<T>(n, -1, B, A, tw, lz, 1, c->stream)) != hipSuccess) return e;
-      if ((e = psms::launch_spec_finish<T>(A, dst, g, 1, dealias, axis, 1.0 / (double(n) * n * n), c->stream)) !=
-          hipSuccess)
+      ra.in_fstride = (long long)nphys;
+      ra.out_fstride = (long long)nfull;
+      const double inv_n3 = 1.0 / (double(n) * n * n);
+      lz.scale = finish ? 1.0 : inv_n3;
+      if ((e = psms::launch_rows<T>(n, -1, src, A, tw, ra, k, c->stream)) != hipSuccess) return e;
+      if ((e = psms::launch_lines<T>(n, -1, A, B, tw, ly, k, c->stream)) != hipSuccess) return e;
+      if ((e = psms::launch_lines<T>(n, -1, B, finish ? A : dst, tw, lz, k, c->stream)) != hipSuccess) return e;
+      if (finish && (e = psms::launch_spec_finish<T>(A, dst, g, k, dealias, axis, inv_n3, c->stream)) != hipSuccess)
         return e;
     } else {
       const cpx<T>* src = static_cast<const cpx<T>*>(d_in) + f * nfull;
       T* dst = static_cast<T*>(d_out) + f * nphys;
-      if ((e = psms::launch_spec_finish<T>(src, A, g, 1, dealias, axis, 1.0, c->stream)) != hipSuccess) return e;
-      if ((e = psms::launch_lines<T>(n, +1, A, B, tw, lz, 1, c->stream)) != hipSuccess) return e;
-      if ((e = psms::launch_lines<T>(n, +1, B, A, tw, ly, 1, c->stream)) != hipSuccess) return e;
+      if (finish && (e = psms::launch_spec_finish<T>(src, A, g, k, dealias, axis, 1.0, c->stream)) != hipSuccess)
+        return e;
+      if ((e = psms::launch_lines<T>(n, +1, finish ? A : src, B, tw, lz, k, c->stream)) != hipSuccess) return e;
+      if ((e = psms::launch_lines<T>(n, +1, B, A, tw, ly, k, c->stream)) != hipSuccess) return e;
       ra.n_in = nh;
       ra.n_out = n;
-      if ((e = psms::launch_rows<T>(n, +1, A, dst, tw, ra, 1, c->stream)) != hipSuccess) return e;
+      ra.in_fstride = (long long)nfull;
+      ra.out_fstride = (long long)nphys;
+      if ((e = psms::launch_rows<T>(n, +1, A, dst, tw, ra, k, c->stream)) != hipSuccess) return e;
     }
   }
   return hipSuccess;
+}
+
+// u, v, w of the state's band on the grid (FP64), through bufa and bufb
+hipError_t velocity_on_grid(psms_ctx* c, double* u, double* v, double* w) {
+  const BoxGeom& g = c->g;
+  const int n = g.n;
+  cpx<double>* A = static_cast<cpx<double>*>(c->bufa);
+  cpx<double>* B = static_cast<cpx<double>*>(c->bufb);
+  psms::LineArgs lz{};
+  lz.n_in = g.C;
+  lz.n_out = n;
+  lz.inner = g.Q;
+  lz.nlines = g.Q;
+  lz.in_fstride = g.M;
+  lz.out_fstride = (long long)n * g.Q;
+  lz.fmap = 0x76543210u;
+  lz.scale = 1.0;
+  psms::LineArgs ly = lz;
+  ly.inner = g.H;
+  ly.nlines = (long long)n * g.H;
+  ly.in_fstride = (long long)n * g.Q;
+  ly.out_fstride = (long long)n * n * g.H;
+  psms::RowArgs ra{};
+  ra.nrows = (long long)n * n;
+  ra.n_in = g.H;
+  ra.n_out = n;
+  ra.scale = 1.0;
+  hipError_t e = psms::launch_lines<double>(n, +1, c->state, B, c->tw64, lz, 3, c->stream);
+  if (e == hipSuccess) e = psms::launch_lines<double>(n, +1, B, A, c->tw64, ly, 3, c->stream);
+  double* out[3] = {u, v, w};
+  for (int k = 0; k < 3 && e == hipSuccess; ++k)
+    e = psms::launch_rows<double>(n, +1, A + k * ly.out_fstride, out[k], c->tw64, ra, 1, c->stream);
+  return e;
 }
 
 bool aligned(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 255u) == 0; }
@@ -530,11 +578,15 @@ int psms_get_state(psms_ctx* c, double* d_uhat, double* d_phihat, double* d_hist
   if (!c || !d_uhat || !d_phihat) return fail(PSMS_E_INVAL, "NULL argument");
   if (!c->have_state) return fail(PSMS_E_STATE, "no state: call psms_init_state or psms_set_state first");
   const BoxGeom& g = c->g;
-  hipError_t e = psms::launch_expand<double>(c->state, reinterpret_cast<cpx<double>*>(d_uhat), g, 3, c->stream);
-  if (e == hipSuccess)
-    e = psms::launch_expand<double>(c->state + 3 * g.M, reinterpret_cast<cpx<double>*>(d_phihat), g, 1, c->stream);
-  if (e == hipSuccess && d_hist)
-    e = psms::launch_expand<double>(c->hist, reinterpret_cast<cpx<double>*>(d_hist), g, 4, c->stream);
+  psms::SpecOut<double> out{};
+  const size_t per = size_t(g.n) * g.n * (g.n / 2 + 1);
+  for (int k = 0; k < 3; ++k) out.p[k] = reinterpret_cast<cpx<double>*>(d_uhat) + k * per;
+  out.p[3] = reinterpret_cast<cpx<double>*>(d_phihat);
+  hipError_t e = psms::launch_expand<double>(c->state, out, g, 4, c->stream);
+  if (e == hipSuccess && d_hist) {
+    for (int k = 0; k < 4; ++k) out.p[k] = reinterpret_cast<cpx<double>*>(d_hist) + k * per;
+    e = psms::launch_expand<double>(c->hist, out, g, 4, c->stream);
+  }
   if (e != hipSuccess) return hip_fail(e, "get_state");
   return PSMS_OK;
 }
@@ -655,38 +707,20 @@ int psms_diagnostics(psms_ctx* c, psms_diag* h_out) {
   if (!c || !h_out) return fail(PSMS_E_INVAL, "NULL argument");
   if (!c->have_state) return fail(PSMS_E_STATE, "no state");
   hipError_t e = psms::launch_diag(c->state, c->g, c->diag, kDiagBlocks, c->diag_out, c->stream);
-  // CFL = dt max_x sum_i |u_i| / dx: each component to physical space (FP64,
-  // through the step's scratch, so the next step re-runs its prologue)
+  // CFL = dt max_x sum_i |u_i| / dx: the velocity in physical space (FP64,
+  // through the step's scratch, so the next step re-runs its prologue; u and v
+  // into the context's two grid fields, w over the z-inverse in bufb, which
+  // holds at least one FP64 half spectrum)
   const BoxGeom& g = c->g;
-  const int n = g.n, nh = n / 2 + 1;
+  const int n = g.n;
   const long long np = (long long)n * n * n;
-  double* phys = reinterpret_cast<double*>(c->ws + c->lay.phys);
-  double* acc = reinterpret_cast<double*>(c->ws + c->lay.acc);
-  cpx<double>* A = static_cast<cpx<double>*>(c->bufa);
-  cpx<double>* B = static_cast<cpx<double>*>(c->bufb);
-  psms::LineArgs ly{};
-  ly.n_in = n;
-  ly.n_out = n;
-  ly.inner = nh;
-  ly.nlines = (long long)n * nh;
-  ly.scale = 1.0;
-  psms::LineArgs lz = ly;
-  lz.inner = (long long)n * nh;
-  psms::RowArgs ra{};
-  ra.nrows = (long long)n * n;
-  ra.n_in = nh;
-  ra.n_out = n;
-  ra.scale = 1.0;
+  double* u = reinterpret_cast<double*>(c->ws + c->lay.phys);
+  double* v = reinterpret_cast<double*>(c->ws + c->lay.acc);
+  double* w = static_cast<double*>(c->bufb);
   c->g_valid = 0;
-  for (int k = 0; k < 3 && e == hipSuccess; ++k) {
-    e = psms::launch_expand<double>(c->state + k * g.M, B, g, 1, c->stream);
-    if (e == hipSuccess) e = psms::launch_spec_finish<double>(B, A, g, 1, 0, -1, 1.0, c->stream);
-    if (e == hipSuccess) e = psms::launch_lines<double>(n, +1, A, B, c->tw64, lz, 1, c->stream);
-    if (e == hipSuccess) e = psms::launch_lines<double>(n, +1, B, A, c->tw64, ly, 1, c->stream);
-    if (e == hipSuccess) e = psms::launch_rows<double>(n, +1, A, phys, c->tw64, ra, 1, c->stream);
-    if (e == hipSuccess) e = psms::launch_abs_accum(phys, acc, np, c->p.dt * n / (2.0 * M_PI), k == 0, c->stream);
-  }
-  if (e == hipSuccess) e = psms::launch_max(acc, np, c->diag, kDiagBlocks, c->diag_out + 5, c->stream);
+  if (e == hipSuccess) e = velocity_on_grid(c, u, v, w);
+  if (e == hipSuccess)
+    e = psms::launch_cfl(u, v, w, np, c->p.dt * n / (2.0 * M_PI), c->diag, kDiagBlocks, c->diag_out + 5, c->stream);
   double h[8];
   if (e == hipSuccess) e = hipMemcpyAsync(h, c->diag_out, sizeof(h), hipMemcpyDeviceToHost, c->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
@@ -734,7 +768,9 @@ hipError_t pressure_impl(psms_ctx* c, double* d_p) {
     e = psms::launch_lines<T>(n, -1, static_cast<const cpx<T>*>(c->bufa), t6, twiddles<T>(c), lz, 6, c->stream);
   cpx<double>* pb = reinterpret_cast<cpx<double>*>(c->ws + c->lay.phys);
   if (e == hipSuccess) e = psms::launch_pressure_band<T>(t6, g, pb, c->stream);
-  if (e == hipSuccess) e = psms::launch_expand<double>(pb, reinterpret_cast<cpx<double>*>(d_p), g, 1, c->stream);
+  psms::SpecOut<double> out{};
+  out.p[0] = reinterpret_cast<cpx<double>*>(d_p);
+  if (e == hipSuccess) e = psms::launch_expand<double>(pb, out, g, 1, c->stream);
   return e;
 }
 }  // namespace
@@ -1461,11 +1497,22 @@ int psms_adjoint_backward(psms_adjoint* a, double* d_dphi0, double* h_dwe) {
       PSMS_TRY(psms::launch_adj_stage(n, 2, a->lam, a->mu, a->adja, nullptr, nullptr, c->tw64, ac, csig, nullptr, S));
     }
   }
-  // dJ/dphi0 on the grid: inv(D lam_phi) / n^3
-  PSMS_TRY(psms::launch_expand<double>(a->lam + 3 * g.M, a->adjb, g, 1, S));
-  PSMS_TRY(psms::launch_spec_finish<double>(a->adjb, a->adjb, g, 1, 0, -1, 1.0 / n3, S));
+  // dJ/dphi0 on the grid: inv(D lam_phi) / n^3, from the band
   c->g_valid = 0;
-  PSMS_TRY(transform_fields<double>(c, -1, 1, a->adjb, d_dphi0, 0));
+  psms::LineArgs lz{};
+  lz.n_in = g.C;
+  lz.n_out = n;
+  lz.inner = g.Q;
+  lz.nlines = g.Q;
+  lz.scale = 1.0 / n3;
+  PSMS_TRY(psms::launch_lines<double>(n, +1, a->lam + 3 * g.M, a->adja, c->tw64, lz, 1, S));
+  PSMS_TRY(y_lines64(c, +1, a->adja, a->adjb, 1));
+  psms::RowArgs ra{};
+  ra.nrows = (long long)n * n;
+  ra.n_in = g.H;
+  ra.n_out = n;
+  ra.scale = 1.0;
+  PSMS_TRY(psms::launch_rows<double>(n, +1, a->adjb, d_dphi0, c->tw64, ra, 1, S));
   PSMS_TRY(hipMemcpyAsync(h_dwe, a->acc, sizeof(double), hipMemcpyDeviceToHost, S));
   PSMS_TRY(hipStreamSynchronize(S));
 #undef PSMS_TRY

@@ -84,8 +84,14 @@ hipError_t launch_step_stage(int n, int stage, int variant, const BoxDev* table,
 template <typename T>
 hipError_t launch_xstage_rows(int n, const BoxDev* dev, const cpx<T>* tw, long long rows, double kxs,
                               hipStream_t st);
+// field f of a compact band [nf][C][C][H] into the full half spectrum out.p[f]
+constexpr int kSpecOutMax = 8;
 template <typename T>
-hipError_t launch_expand(const cpx<T>* cmp, cpx<T>* full, const BoxGeom& g, int nf, hipStream_t st);
+struct SpecOut {
+  cpx<T>* p[kSpecOutMax];
+};
+template <typename T>
+hipError_t launch_expand(const cpx<T>* cmp, const SpecOut<T>& out, const BoxGeom& g, int nf, hipStream_t st);
 template <typename T>
 hipError_t launch_compact(const cpx<T>* full, cpx<T>* cmp, const BoxGeom& g, int nf, hipStream_t st);
 hipError_t launch_project(cpx<double>* u, const BoxGeom& g, hipStream_t st);
@@ -105,10 +111,9 @@ hipError_t launch_spec_finish(const cpx<T>* in, cpx<T>* out, const BoxGeom& g, i
 hipError_t launch_helmholtz_box(const cpx<double>* rhs, cpx<double>* out, const BoxGeom& g, double lam,
                                 hipStream_t st);
 hipError_t launch_index_maps(int* out, const BoxGeom& g, hipStream_t st);
-// acc = (first ? 0 : acc) + scale |f| over n values
-hipError_t launch_abs_accum(const double* f, double* acc, long long n, double scale, int first, hipStream_t st);
-// out[0] = max of a[0..n) (a >= 0), two passes through part[max_blocks]
-hipError_t launch_max(const double* a, long long n, double* part, int max_blocks, double* out, hipStream_t st);
+// out[0] = max over n points of scale (|u| + |v| + |w|), two passes through part[max_blocks]
+hipError_t launch_cfl(const double* u, const double* v, const double* w, long long n, double scale, double* part,
+                      int max_blocks, double* out, hipStream_t st);
 hipError_t launch_diag(const cpx<double>* state, const BoxGeom& g, double* part, int max_blocks, double* out,
                        hipStream_t st);
 

@@ -15,7 +15,7 @@ LIB = os.path.join(HERE, "libpsms.so")
 
 # (source, extra flags): box_kernels.hip in two parts, which compile side by side
 SOURCES = [("box_kernels.hip", ["-DPSMS_PART=64"]), ("box_kernels.hip", ["-DPSMS_PART=32"]),
-           ("channel_kernels.hip", []), ("channel_step_kernels.hip", []), ("adjoint_kernels.hip", []),
+           ("channel_kernels.hip", []), ("channel_tau.hip", []), ("channel_step_kernels.hip", []), ("adjoint_kernels.hip", []),
            ("api.cpp", [])]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

@@ -13,6 +13,7 @@
 #include "../../include/psms.h"
 #include "box_kernels.hpp"
 #include "channel_kernels.hpp"
+#include "channel_tau.hpp"
 #include "adjoint_kernels.hpp"
 #include "channel_step_kernels.hpp"
 
@@ -949,6 +950,14 @@ int psms_wall_solve(const psms_wall_args* a, void* d_work, size_t bytes, void* s
   hipError_t e;
 #define PSMS_TRY(x) \
   if ((e = (x)) != hipSuccess) return hip_fail(e, "wall_solve")
+  if (psms::tau_pieces_nc(nc)) {
+    const psms::WallTauArgs t{CC(a->d_g_om), CC(a->d_g_w), CC(a->d_g_phi), CM(a->d_om), CM(a->d_w), CM(a->d_phi),
+                              a->d_kx, a->d_ky, nl, a->beta_ns, a->beta_a, a->beta_b};
+    PSMS_TRY(psms::launch_wall_tau(t, nc, st));
+    PSMS_TRY(psms::launch_cheb_uv(CC(a->d_om), CC(a->d_w), CM(a->d_u), CM(a->d_v), nc, nl, a->d_kx, a->d_ky, st));
+    return PSMS_OK;
+  }
+  // chain lengths outside the pieced solves: one lane per chain
   // the independent problems share a launch: omega_z and the three psi
   // problems of w (particular, unit value at the top, at the bottom); then w
   // from each psi and the first CH factor; then phi; then the influence-matrix
@@ -970,9 +979,7 @@ int psms_wall_solve(const psms_wall_args* a, void* d_work, size_t bytes, void* s
   b.p[0] = psms::HelmProblem{C(L.xi), CM(a->d_phi), xw, nl, a->beta_b, a->d_kx, a->d_ky, 3, z0, z0};
   PSMS_TRY(psms::launch_helm_batch(b, nc, st));
   PSMS_TRY(psms::launch_influence(CM(a->d_w), C(L.wt), C(L.wb), nc, nl, a->d_kx, a->d_ky, st));
-  // u, v
-  PSMS_TRY(psms::launch_chebd(CM(a->d_w), C(L.dw), nc, nl, st));
-  PSMS_TRY(psms::launch_uv(CM(a->d_om), C(L.dw), CM(a->d_u), CM(a->d_v), nc, nl, a->d_kx, a->d_ky, st));
+  PSMS_TRY(psms::launch_cheb_uv(CC(a->d_om), CC(a->d_w), CM(a->d_u), CM(a->d_v), nc, nl, a->d_kx, a->d_ky, st));
 #undef PSMS_TRY
   return PSMS_OK;
 }

@@ -18,12 +18,13 @@
 //    (the banded wall-normal solves of Sec. 3.2.2).  k_helm_batch_reg keeps a
 //    chain on chip; k_helm_factors stores a context's elimination factors,
 //    from which k_helm_pieces solves each chain in 8 pieces (affine-map scans).
-//  * k_influence, k_uv: the influence-matrix combination that enforces
-//    w' = 0 at the walls, and u, v from continuity and eq. omegadef.
+//  * k_influence: the influence-matrix combination that enforces w' = 0 at the
+//    walls; k_cheb_uv: u, v from continuity and eq. omegadef.
 #include <hip/hip_runtime.h>
 
 #include "channel_kernels.hpp"
 #include "fft_engine.hpp"
+#include "tau_rows.hpp"
 
 namespace psms {
 
@@ -508,6 +509,59 @@ __global__ void __launch_bounds__(256) k_cheb_seg_q(ChebQ in, int nc, long long 
     }
   }
 }
+// u = i (kx D w + ky omega) / k^2, v = i (ky D w - kx omega) / k^2 (0 where k = 0),
+// D w by the pieced recurrence of k_cheb_seg in the same pass: w and omega are
+// read once and u, v written (7310 lines x 129: 12.0 us; the derivative and the
+// combination as two passes 20.4).
+template <int LEN, int PC>
+__global__ void __launch_bounds__(256) k_cheb_uv(const cpx<double>* __restrict__ om, const cpx<double>* __restrict__ w,
+                                                 int nc, long long nlines, const double* __restrict__ kxl,
+                                                 const double* __restrict__ kyl, cpx<double>* __restrict__ u,
+                                                 cpx<double>* __restrict__ v) {
+  constexpr int LPW = 64 / PC;   // lines per wavefront
+  const int lane = threadIdx.x & 63;
+  const int pc = lane / LPW;
+  const long long groups = (nlines + LPW - 1) / LPW;
+  const long long wave = ((long long)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+  if (wave >= 2 * groups) return;   // whole wavefronts
+  const int q = int(wave / groups);
+  const long long l = (wave % groups) * LPW + (lane % LPW);
+  const bool valid = l < nlines;
+  const double kx = valid ? kxl[l] : 0.0, ky = valid ? kyl[l] : 0.0, k2 = kx * kx + ky * ky;
+  const double ik = k2 != 0.0 ? 1.0 / k2 : 0.0;
+  const int top = ((nc - q) & 1) ? nc - 1 : nc;
+  const int cnt = top / 2 + 1;
+  const int i0 = pc * LEN;
+  cpx<double> x[LEN], o[LEN];
+#pragma unroll
+  for (int k = 0; k < LEN; ++k) {
+    const int m = top - 2 * (i0 + k);
+    x[k] = o[k] = cpx<double>{0.0, 0.0};
+    if (valid && i0 + k < cnt) {
+      if (m + 1 <= nc) {
+        const cpx<double> a = w[(long long)(m + 1) * nlines + l];
+        x[k] = cpx<double>{2.0 * (m + 1) * a.re, 2.0 * (m + 1) * a.im};
+      }
+      o[k] = om[(long long)m * nlines + l];
+    }
+  }
+#pragma unroll
+  for (int k = 1; k < LEN; ++k) x[k] = cadd(x[k - 1], x[k]);
+  const cpx<double> c = piece_carry<PC>(x[LEN - 1], pc);
+#pragma unroll
+  for (int k = 0; k < LEN; ++k) {
+    const int m = top - 2 * (i0 + k);
+    if (valid && i0 + k < cnt) {
+      const double s = (m == 0) ? 0.5 : 1.0;
+      const cpx<double> d = {s * (c.re + x[k].re), s * (c.im + x[k].im)};
+      const cpx<double> su = {kx * d.re + ky * o[k].re, kx * d.im + ky * o[k].im};
+      const cpx<double> sv = {ky * d.re - kx * o[k].re, ky * d.im - kx * o[k].im};
+      const bool mean = k2 == 0.0;   // left to the mean flow
+      u[(long long)m * nlines + l] = mean ? cpx<double>{0.0, 0.0} : cpx<double>{-su.im * ik, su.re * ik};
+      v[(long long)m * nlines + l] = mean ? cpx<double>{0.0, 0.0} : cpx<double>{-sv.im * ik, sv.re * ik};
+    }
+  }
+}
 }  // namespace
 
 // Chebyshev-tau Helmholtz solve (D^2 - beta) f = g, one thread per (line,
@@ -528,25 +582,7 @@ __global__ void __launch_bounds__(256) k_cheb_seg_q(ChebQ in, int nc, long long 
 // plus the constants top_c, bot_c.  g may be NULL (zero).  xw: nc+1 doubles
 // per line of scratch.
 
-// The coefficients of the tau rows that depend only on the index n:
-// q1 = 1 / (4 n (n - 1)), q2 = 1 / (2 (n^2 - 1)), q3 = 1 / (4 n (n + 1)), n >= 2,
-// evaluated at compile time (correctly rounded, as the run-time division would
-// be) and read with wave-uniform addresses, so no recurrence step divides by them.
-struct TauQ {
-  double q[3][kTauQMax + 1];
-};
 constexpr int kHelmPieces = 8;   // pieces per chain in k_helm_pieces
-constexpr TauQ make_tau_q() {
-  TauQ t{};
-  for (int n = 2; n <= kTauQMax; ++n) {
-    const double dn = double(n);
-    t.q[0][n] = 1.0 / (4.0 * dn * (dn - 1.0));
-    t.q[1][n] = 1.0 / (2.0 * (dn * dn - 1.0));
-    t.q[2][n] = 1.0 / (4.0 * dn * (dn + 1.0));
-  }
-  return t;
-}
-__constant__ TauQ kTauQ = make_tau_q();
 
 // downward sweep of parity p: a_i = X_i a_{i-1} + Y_i for the indices
 // n = p + 2 i, i = m..1 (X in xw, Y in f)
@@ -1199,30 +1235,6 @@ __global__ void __launch_bounds__(256) k_influence_apply(cpx<double>* __restrict
   }
 }
 
-// u = i (kx w' + ky omega) / k^2, v = i (ky w' - kx omega) / k^2 (0 where k = 0).
-__global__ void k_uv(const cpx<double>* __restrict__ om, const cpx<double>* __restrict__ dw, cpx<double>* __restrict__ u,
-                     cpx<double>* __restrict__ v, int nc, long long nlines, const double* __restrict__ kx,
-                     const double* __restrict__ ky) {
-  const long long tot = (long long)(nc + 1) * nlines;
-  for (long long id = (long long)blockIdx.x * blockDim.x + threadIdx.x; id < tot;
-       id += (long long)gridDim.x * blockDim.x) {
-    const long long l = id % nlines;
-    const double a = kx[l], b = ky[l];
-    const double k2 = a * a + b * b;
-    cpx<double> uu = {0.0, 0.0}, vv = {0.0, 0.0};
-    if (k2 != 0.0) {
-      const double ik = 1.0 / k2;
-      const cpx<double> o = om[id], d = dw[id];
-      const cpx<double> su = {a * d.re + b * o.re, a * d.im + b * o.im};
-      const cpx<double> sv = {b * d.re - a * o.re, b * d.im - a * o.im};
-      uu = cpx<double>{-su.im * ik, su.re * ik};
-      vv = cpx<double>{-sv.im * ik, sv.re * ik};
-    }
-    u[id] = uu;
-    v[id] = vv;
-  }
-}
-
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
@@ -1458,12 +1470,21 @@ hipError_t launch_influence_apply(cpx<double>* wp, const cpx<double>* wt, const 
   return hipGetLastError();
 }
 
-hipError_t launch_uv(const cpx<double>* om, const cpx<double>* dw, cpx<double>* u, cpx<double>* v, int nc,
-                     long long nlines, const double* kx, const double* ky, hipStream_t st) {
-  long long b = ((long long)(nc + 1) * nlines + 255) / 256;
-  if (b > 65536) b = 65536;
-  k_uv<<<unsigned(b < 1 ? 1 : b), 256, 0, st>>>(om, dw, u, v, nc, nlines, kx, ky);
-  return hipGetLastError();
+hipError_t launch_cheb_uv(const cpx<double>* om, const cpx<double>* w, cpx<double>* u, cpx<double>* v, int nc,
+                          long long nlines, const double* kx, const double* ky, hipStream_t st) {
+  if (nlines < 0 || nc < 1) return hipErrorInvalidValue;
+  if (nlines == 0) return hipSuccess;
+  const int need = (nc / 2 + 1 + 7) / 8;
+  const int pcs = need <= 9 ? 8 : 16;   // as in launch_cheb_batch
+  const dim3 grid(blocks(2 * ((nlines + 64 / pcs - 1) / (64 / pcs)) * 64, 256));
+#define PSMS_SEG(LEN, PCS) \
+  if (pcs == PCS && (nc / 2 + PCS) / PCS <= LEN) { \
+    k_cheb_uv<LEN, PCS><<<grid, 256, 0, st>>>(om, w, nc, nlines, kx, ky, u, v); \
+    return hipGetLastError(); \
+  }
+  PSMS_SEG(1, 8) PSMS_SEG(2, 8) PSMS_SEG(3, 8) PSMS_SEG(5, 8) PSMS_SEG(9, 8) PSMS_SEG(9, 16)
+#undef PSMS_SEG
+  return hipErrorInvalidValue;   // nc > 287
 }
 
 template hipError_t launch_dct<double>(int, const cpx<double>*, cpx<double>*, long long, int, hipStream_t);

@@ -9,7 +9,6 @@
 namespace psms {
 
 bool supported_nc(int nc);
-constexpr int kTauQMax = 256;   // largest nc of the tau solves
 
 template <typename T>
 hipError_t launch_dct(int nc, const cpx<T>* in, cpx<T>* out, long long nlines, int dir, hipStream_t st);
@@ -131,7 +130,8 @@ hipError_t launch_influence_pre(const cpx<double>* wt, const cpx<double>* wb, in
 hipError_t launch_influence_apply(cpx<double>* wp, const cpx<double>* wt, const cpx<double>* wb, const double* M,
                                   int nc, long long nlines, const double* kx, const double* ky, int free_slip,
                                   hipStream_t st);
-hipError_t launch_uv(const cpx<double>* om, const cpx<double>* dw, cpx<double>* u, cpx<double>* v, int nc,
-                     long long nlines, const double* kx, const double* ky, hipStream_t st);
+// u, v from omega and w (continuity and eq. omegadef; zero where kx = ky = 0)
+hipError_t launch_cheb_uv(const cpx<double>* om, const cpx<double>* w, cpx<double>* u, cpx<double>* v, int nc,
+                          long long nlines, const double* kx, const double* ky, hipStream_t st);
 
 }  // namespace psms

@@ -60,3 +60,25 @@ def test_transform_chunks_of_fields(n, precision, flags):
     psms._check(psms.lib().psms_transform(s.ctx, -1, 9, psms._ptr(fh), psms._ptr(fh), flags))
     inplace = torch.view_as_real(fh).reshape(-1)[: 9 * n ** 3].reshape(9, n, n, n)
     assert torch.equal(inplace, back)
+
+
+# The pieced wall solves: chains shorter than the 8 pieces (nc = 4 .. 12), with a partly
+# filled last piece, line counts around the 64 of a workgroup, and (nc = 20, 33) the
+# lengths that keep the one-lane-per-chain solve.  Bar: 1e-11 of each line's largest
+# coefficient, as for the other wall-solve tests.
+@pytest.mark.parametrize("nc,nl", [(4, 1), (6, 63), (8, 64), (12, 65), (24, 3), (48, 5), (64, 129), (96, 2), (256, 66),
+                                   (20, 7), (33, 7)])
+def test_pieced_wall_solve_sizes(nc, nl):
+    from oracle import channel as ch
+    from paper_2406_01322_amd import psms
+    rng = np.random.default_rng(nc)
+    kx, ky = np.arange(nl) % 7 * 0.5, (np.arange(nl) // 7 - 2) * 1.0      # a mean line from nl = 15 on
+    g = [(rng.standard_normal((nc + 1, nl)) + 1j * rng.standard_normal((nc + 1, nl)))
+         * np.exp(-0.05 * np.arange(nc + 1))[:, None] for _ in range(3)]
+    bn, ba, bb = 3e4, 40.0, 700.0
+    k2 = kx ** 2 + ky ** 2
+    want = ch.wall_normal_solve_lines(*g, kx, ky, k2 + bn, k2 + ba, k2 + bb)
+    got = psms.wall_solve(_dev(kx), _dev(ky), bn, ba, bb, *[_dev(x) for x in g])
+    for key in ("omega", "w", "phi", "u", "v"):
+        a, b = _host(got[key]), want[key]
+        assert np.all(np.max(np.abs(a - b), axis=0) <= 1e-11 * np.max(np.abs(b), axis=0)), key

@@ -973,10 +973,10 @@ int psms_wall_solve(const psms_wall_args* a, void* d_work, size_t bytes, void* s
   b.p[0] = psms::HelmProblem{C(L.psi), CM(a->d_w), xw, nl, 0.0, a->d_kx, a->d_ky, 0, z0, z0};
   b.p[1] = psms::HelmProblem{C(L.psit), C(L.wt), xw + xs, nl, 0.0, a->d_kx, a->d_ky, 0, z0, z0};
   b.p[2] = psms::HelmProblem{C(L.psib), C(L.wb), xw + 2 * xs, nl, 0.0, a->d_kx, a->d_ky, 0, z0, z0};
-  b.p[3] = psms::HelmProblem{CC(a->d_g_phi), C(L.xi), xw + 3 * xs, nl, a->beta_a, a->d_kx, a->d_ky, 3, z0, z0};
+  b.p[3] = psms::HelmProblem{CC(a->d_g_phi), C(L.xi), xw + 3 * xs, nl, a->beta_a, a->d_kx, a->d_ky, 1, z0, z0};
   PSMS_TRY(psms::launch_helm_batch(b, nc, st));
   b.np = 1;
-  b.p[0] = psms::HelmProblem{C(L.xi), CM(a->d_phi), xw, nl, a->beta_b, a->d_kx, a->d_ky, 3, z0, z0};
+  b.p[0] = psms::HelmProblem{C(L.xi), CM(a->d_phi), xw, nl, a->beta_b, a->d_kx, a->d_ky, 1, z0, z0};
   PSMS_TRY(psms::launch_helm_batch(b, nc, st));
   PSMS_TRY(psms::launch_influence(CM(a->d_w), C(L.wt), C(L.wb), nc, nl, a->d_kx, a->d_ky, st));
   PSMS_TRY(psms::launch_cheb_uv(CC(a->d_om), CC(a->d_w), CM(a->d_u), CM(a->d_v), nc, nl, a->d_kx, a->d_ky, st));
@@ -1536,14 +1536,8 @@ namespace {
 struct ChanLayout {
   size_t kx, ky, twx64, twx32, twy64, twy32, twz64, twz32;
   size_t state, mean, hist, hmean;
-  size_t dw, dphi, A, A2, B, C, R, D3, DQ, lapc, lapom, lappsi, G;
-  size_t d2mean, gmean, wt, wb, M, whp, mhp, psip, xi, xw, diag, xdev, fac, total;
-  bool has_fac;   // the step's tau problems read precomputed elimination factors
+  size_t dw, dphi, A, A2, B, C, R, whp, mhp, diag, xdev, total;
 };
-
-// the step's six tau problems (omega_z, psi_p, the mean line, xi, w_p, phi)
-// each keep a table of elimination factors, in this order
-enum { kChanFacOm, kChanFacPsi, kChanFacMean, kChanFacXi, kChanFacW, kChanFacPhi, kChanFacCount };
 
 constexpr int kChanDiagBlocks = 1024;   // partial sums of the diagnostics
 
@@ -1598,27 +1592,8 @@ ChanLayout chan_layout(const psms_channel_params& p) {
   take(L.B, 8 * nz * size_t(p.ny) * size_t(g.Hx) * t);
   take(L.C, 8 * size_t(g.P) * tr);
   take(L.R, 8 * arr);
-  take(L.D3, 3 * arr);
-  take(L.DQ, arr);
-  take(L.lapc, arr);
-  take(L.lapom, arr);
-  take(L.lappsi, arr);
-  take(L.G, 3 * arr);
-  take(L.d2mean, 2 * nz * c64);
-  take(L.gmean, 2 * nz * c64);
-  take(L.wt, arr);
-  take(L.wb, arr);
-  take(L.M, 4 * size_t(g.NL) * sizeof(double));
   take(L.whp, nz * size_t(g.NL) * sizeof(double));
   take(L.mhp, 2 * size_t(g.NL) * sizeof(double));
-  take(L.psip, arr);
-  take(L.xi, arr);
-  // elimination factors of the tau problems: kept where the solves stay on
-  // chip (same condition at both walls and a chain length the kernels unroll)
-  const int fsw = p.free_slip & 3;
-  L.has_fac = (fsw == 0 || fsw == 3) && psms::helm_fuses_influence(p.nc);
-  take(L.fac, L.has_fac ? kChanFacCount * psms::helm_factor_doubles(p.nc, g.NL) * sizeof(double) : 0);
-  take(L.xw, 4 * nz * size_t(g.NL) * sizeof(double));   // one elimination scratch per batched problem
   take(L.diag, (8 * size_t(kChanDiagBlocks) + 8) * sizeof(double));
   take(L.xdev, sizeof(psms::BoxDev));   // descriptor of the fused x stage
   L.total = off;
@@ -1660,6 +1635,7 @@ struct psms_channel {
   double a_fac, b_fac;
   int nstep;
   int have_state;
+  int d_valid;   // D w, D phi of the current state are in the workspace (the step leaves them)
   template <typename X>
   X* at(size_t off) const {
     return reinterpret_cast<X*>(ws + off);
@@ -1679,14 +1655,11 @@ const cpx<T>* chan_twz(const psms_channel* c) {
   return reinterpret_cast<const cpx<T>*>(c->ws + (std::is_same<T, double>::value ? c->lay.twz64 : c->lay.twz32));
 }
 
-// x-spectral [nf][z][y][kx band] (T) -> band [nf][n][line] (T): y lines (1/(nx ny)),
-// DCT-I; with band64, the DCT-I writes FP64 coefficients there instead, n > Kz zeroed
+// x-spectral [nf][z][y][kx band] (T) -> A2 [nf][z][line] (T): y lines (1/(nx ny))
 template <typename T>
-hipError_t chan_forward_yz(psms_channel* c, const cpx<T>* xs, cpx<T>* band, int nf, cpx<double>* band64) {
+hipError_t chan_forward_y(psms_channel* c, const cpx<T>* xs, int nf) {
   const psms::ChanGeom& g = c->g;
   const long long nz = g.nc + 1;
-  cpx<T>* A2 = c->at<cpx<T>>(c->lay.A2);
-  hipError_t e;
   psms::LineArgs la{};
   la.n_in = g.ny;
   la.n_out = g.Cy;
@@ -1697,15 +1670,12 @@ hipError_t chan_forward_yz(psms_channel* c, const cpx<T>* xs, cpx<T>* band, int 
   la.fmap = 0x76543210u;
   la.dmask = 0;
   la.scale = 1.0 / (double(g.nx) * double(g.ny));
-  e = psms::launch_lines<T>(g.ny, -1, xs, A2, chan_tw<T>(c, false), la, nf, c->stream);
-  if (e == hipSuccess)
-    e = psms::launch_dct_fields<T>(g.nc, A2, band, g.NL, g.NZL, nf, chan_twz<T>(c), +1, c->stream, band64, g.Kz);
-  return e;
+  return psms::launch_lines<T>(g.ny, -1, xs, c->at<cpx<T>>(c->lay.A2), chan_tw<T>(c, false), la, nf, c->stream);
 }
 
-// physical [nf][z][y][x] (T) -> band [nf][n][line] (T): x rows, then chan_forward_yz
+// physical [nf][z][y][x] (T) -> A2 [nf][z][line] (T): x rows, y lines
 template <typename T>
-hipError_t chan_forward(psms_channel* c, const T* phys, cpx<T>* band, int nf, cpx<double>* band64 = nullptr) {
+hipError_t chan_forward_xy(psms_channel* c, const T* phys, int nf) {
   const psms::ChanGeom& g = c->g;
   const long long nz = g.nc + 1;
   cpx<T>* B = c->at<cpx<T>>(c->lay.B);
@@ -1716,9 +1686,8 @@ hipError_t chan_forward(psms_channel* c, const T* phys, cpx<T>* band, int nf, cp
   ra.in_fstride = g.P;
   ra.out_fstride = nz * g.ny * g.Hx;
   ra.scale = 1.0;
-  hipError_t e = psms::launch_rows<T>(g.nx, -1, phys, B, chan_tw<T>(c, true), ra, nf, c->stream);
-  if (e != hipSuccess) return e;
-  return chan_forward_yz<T>(c, B, band, nf, band64);
+  const hipError_t e = psms::launch_rows<T>(g.nx, -1, phys, B, chan_tw<T>(c, true), ra, nf, c->stream);
+  return e == hipSuccess ? chan_forward_y<T>(c, B, nf) : e;
 }
 
 // band [nf][n][line] (T) -> x-spectral [nf][z][y][kx band] (T) in the buffer B:
@@ -1765,6 +1734,18 @@ hipError_t chan_inverse(psms_channel* c, const cpx<T>* band, T* phys, int nf) {
   return psms::launch_rows<T>(g.nx, +1, B, phys, chan_tw<T>(c, true), ra, nf, c->stream);
 }
 
+// D w and D phi of the state, which the fields of a step are formed from
+hipError_t chan_derivatives(psms_channel* c) {
+  const psms::ChanGeom& g = c->g;
+  cpx<double>* w = c->at<cpx<double>>(c->lay.state) + g.NZL;
+  const hipError_t e = psms::launch_tau_deriv(w, w + g.NZL, c->at<cpx<double>>(c->lay.dw),
+                                              c->at<cpx<double>>(c->lay.dphi), g.sp ? 1 : 2, g.nc, g.NL, c->stream);
+  if (e == hipSuccess) c->d_valid = 1;
+  return e;
+}
+
+// One step from a state whose D w, D phi are in the workspace; it leaves those
+// of the new state there.
 template <typename T>
 hipError_t chan_step_once(psms_channel* c) {
   const psms::ChanGeom& g = c->g;
@@ -1778,132 +1759,61 @@ hipError_t chan_step_once(psms_channel* c) {
   cpx<double>* phi = w + g.NZL;
   const double* kx = c->at<double>(L.kx);
   const double* ky = c->at<double>(L.ky);
-  cpx<double>* R = C64(L.R);
   hipError_t e;
 #define PSMS_TRY(x) \
   if ((e = (x)) != hipSuccess) return e
-  // 1-2. fields and the inverse transforms
-  psms::ChebBatch cb{};
-  cb.n = g.sp ? 1 : 2;
-  cb.in[0] = w;
-  cb.out[0] = C64(L.dw);
-  cb.in[1] = phi;
-  cb.out[1] = C64(L.dphi);
-  PSMS_TRY(psms::launch_cheb_batch(cb, nc, nl, kx, ky, 0, st));
   if (g.sp) {
     PSMS_TRY(psms::launch_ch_fields<T>(g, om, w, phi, C64(L.dw), C64(L.dphi), C64(L.mean), kx, ky,
                                        c->at<cpx<T>>(L.A), st));
     PSMS_TRY(chan_inverse<T>(c, c->at<cpx<T>>(L.A), c->at<T>(L.C), g.nf_in));
-    // 3-4. products and the forward transforms, 2/3 rule in x, y and z
     PSMS_TRY(psms::launch_ch_products<T>(g, c->at<T>(L.C), c->coef.csig, st));
-    PSMS_TRY(chan_forward<T>(c, c->at<T>(L.C), c->at<cpx<T>>(L.A), g.nf_out, R));   // FP64, Chebyshev cut
+    PSMS_TRY(chan_forward_xy<T>(c, c->at<T>(L.C), g.nf_out));
   } else {
     // two-phase: u, v, w, phi, dy phi, dz phi through the DCT-I (each formed from
     // the state as the transform loads it) and y lines; the x-inverse, the 8
     // products and the x-forward in one pass (the box's x stage on (nc + 1) ny
     // rows; dx phi formed on load), so that no physical field is stored; then y
-    // lines and the DCT-I with the Chebyshev cut (FP64)
+    // lines
     const psms::ChanFieldSrc fs{om, w, phi, C64(L.dw), C64(L.dphi), C64(L.mean), kx, ky, nl};
     PSMS_TRY(chan_inverse_yz<T>(c, nullptr, 6, &fs));
     PSMS_TRY(psms::launch_xstage_rows<T>(g.nx, c->at<psms::BoxDev>(L.xdev), chan_tw<T>(c, true),
                                          (long long)(nc + 1) * g.ny, 2.0 * M_PI / c->p.lx, st));
-    PSMS_TRY(chan_forward_yz<T>(c, c->at<cpx<T>>(L.C), c->at<cpx<T>>(L.A), 8, R));
+    PSMS_TRY(chan_forward_y<T>(c, c->at<cpx<T>>(L.C), 8));
   }
-  // 5. the wall-normal derivatives the right-hand sides need, in one launch:
-  // D T_xz, D T_yz, D T_zz; (D^2 - k^2 + beta) omega_z; (D^2 - k^2 + beta) psi,
-  // psi = (D^2 - k^2) w (its chain is in the same wavefront); D^2 - k^2 of
-  // c / Pe - (1 + s Ch^2) / Pe phi; D^2 of the mean lines; then D Q (Q =
-  // div_h S, S = div T, formed on the fly)
-  cpx<double>* D3 = C64(L.D3);
-  cb.n = g.sp ? 6 : 7;
-  cb.in[0] = R + 4 * g.NZL;
-  cb.out[0] = D3;
-  cb.in[1] = R + 5 * g.NZL;
-  cb.out[1] = D3 + g.NZL;
-  cb.in[2] = R + 2 * g.NZL;
-  cb.out[2] = D3 + 2 * g.NZL;
-  cb.in[3] = om;
-  cb.out[3] = C64(L.lapom);
-  cb.addb[3] = c->coef.beta;
-  cb.in[4] = w;
-  cb.out[4] = nullptr;            // psi itself is not needed
-  cb.out2[4] = C64(L.lappsi);
-  cb.addb2[4] = c->coef.beta;
-  if (!g.sp) {
-    cb.in[5] = R + 7 * g.NZL;
-    cb.in2[5] = phi;
-    cb.w1[5] = c->coef.inv_pe;
-    cb.w2[5] = -c->coef.e_coef;
-    cb.out[5] = C64(L.lapc);
-  }
-  const int mj = g.sp ? 5 : 6;   // the mean lines U, V ([nc+1][2], k = 0): D^2
-  cb.in[mj] = C64(L.mean);
-  cb.out[mj] = C64(L.d2mean);
-  cb.nl[mj] = 2;
-  cb.nok = 1 << mj;
-  PSMS_TRY(psms::launch_cheb_batch(cb, nc, nl, kx, ky, 0xF8, st));   // arrays 3.. : D^2 - k^2
-  psms::ChebQ cq{R, R + g.NZL, R + 3 * g.NZL, D3, D3 + g.NZL};
-  PSMS_TRY(psms::launch_chebd_q(cq, nc, nl, kx, ky, C64(L.DQ), st));
-  // 6. Adams-Bashforth, Crank-Nicolson / implicit Euler right-hand sides
-  c->coef.ab1 = (c->nstep == 0) ? 1 : 0;
-  psms::ChanAssembleArgs aa{};
-  aa.d3 = D3;
-  aa.dq = C64(L.DQ);
-  aa.R = R;
-  aa.lsphi = C64(L.lapc);
-  aa.phi = phi;
-  aa.lom = C64(L.lapom);
-  aa.lpsi = C64(L.lappsi);
-  aa.kx = kx;
-  aa.ky = ky;
-  aa.hist = C64(L.hist);
-  aa.g = C64(L.G);
-  aa.mean = C64(L.mean);
-  aa.d2mean = C64(L.d2mean);
-  aa.hmean = C64(L.hmean);
-  aa.gmean = C64(L.gmean);
-  PSMS_TRY(psms::launch_ch_assemble(g, c->coef, aa, st));
-  // the wall-normal solves of every (kx, ky) pair (psms_wall_solve's sequence with
-  // the homogeneous w solutions and their influence matrix precomputed at
-  // creation), and the mean flow; independent problems share a launch
-  const cpx<double> z0 = {0.0, 0.0};
-  double* xw = c->at<double>(L.xw);
-  const long long xws = (long long)(nc + 1) * nl;
-  psms::HelmBatch b1{};
-  b1.np = g.sp ? 3 : 4;
-  const int fs = c->p.free_slip & 3;   // omega_z and U, V: Neumann at a free-slip wall
-  b1.p[0] = psms::HelmProblem{C64(L.G), om, xw, nl, c->coef.beta, kx, ky, fs, z0, z0};                     // omega_z
-  b1.p[1] = psms::HelmProblem{C64(L.G) + g.NZL, C64(L.psip), xw + xws, nl, c->coef.beta, kx, ky, 0, z0, z0};  // psi_p
-  b1.p[2] = psms::HelmProblem{C64(L.gmean), C64(L.mean), xw + 2 * xws, 2, c->coef.beta, nullptr, nullptr, fs, z0,
-                              z0};                                                                        // U, V
-  b1.p[3] = psms::HelmProblem{C64(L.G) + 2 * g.NZL, C64(L.xi), xw + 3 * xws, nl, c->a_fac, kx, ky, 3, z0, z0};  // xi
-  const size_t fd = psms::helm_factor_doubles(nc, nl);
-  const double* fac = L.has_fac ? c->at<double>(L.fac) : nullptr;
-  if (fac) {
-    b1.p[0].fac = fac + kChanFacOm * fd;
-    b1.p[1].fac = fac + kChanFacPsi * fd;
-    b1.p[2].fac = fac + kChanFacMean * fd;
-    b1.p[3].fac = fac + kChanFacXi * fd;   // (not among the np problems in single phase)
-  }
-  PSMS_TRY(psms::launch_helm_batch(b1, nc, st));
-  psms::HelmBatch b2{};
-  b2.np = g.sp ? 1 : 2;
-  b2.p[0] = psms::HelmProblem{C64(L.psip), w, xw, nl, 0.0, kx, ky, 0, z0, z0};             // w_p
-  b2.p[1] = psms::HelmProblem{C64(L.xi), phi, xw + xws, nl, c->b_fac, kx, ky, 3, z0, z0};  // phi
-  // between two no-slip walls the influence correction is applied by the w
-  // chains themselves (the two wall conditions split by parity)
-  const bool fused = (fs == 0) && psms::helm_fuses_influence(nc);
-  if (fused) {
-    b2.p[0].wh = c->at<double>(L.whp);
-    b2.p[0].mh = c->at<double>(L.mhp);
-  }
-  if (fac) {
-    b2.p[0].fac = fac + kChanFacW * fd;
-    b2.p[1].fac = fac + kChanFacPhi * fd;   // (not among the np problems in single phase)
-  }
-  PSMS_TRY(psms::launch_helm_batch(b2, nc, st));
-  if (!fused)
-    PSMS_TRY(psms::launch_influence_apply(w, C64(L.wt), C64(L.wb), c->at<double>(L.M), nc, nl, kx, ky, fs, st));
+  // the products' combinations through the DCT-I with the Chebyshev cut (FP64),
+  // then everything wall-normal in one launch
+  PSMS_TRY(psms::launch_dct_chterms<T>(nc, c->at<cpx<T>>(L.A2), C64(L.R), nl, g.NZL, g.sp ? 4 : 6, kx, ky,
+                                       chan_twz<T>(c), g.Kz, st));
+  psms::ChanTauArgs a{};
+  a.terms = C64(L.R);
+  a.nzl = g.NZL;
+  a.kz = g.Kz;
+  a.om = om;
+  a.w = w;
+  a.phi = phi;
+  a.hist = C64(L.hist);
+  a.mean = C64(L.mean);
+  a.hmean = C64(L.hmean);
+  a.dw = C64(L.dw);
+  a.dphi = C64(L.dphi);
+  a.kx = kx;
+  a.ky = ky;
+  a.wh = c->at<double>(L.whp);
+  a.mh = c->at<double>(L.mhp);
+  a.nl = nl;
+  a.re = c->coef.re;
+  a.beta = c->coef.beta;
+  a.dt = c->coef.dt;
+  a.forcing = c->coef.forcing;
+  a.inv_pe = c->coef.inv_pe;
+  a.e_coef = c->coef.e_coef;
+  a.g_phi_scale = c->coef.g_phi_scale;
+  a.a_fac = c->a_fac;
+  a.b_fac = c->b_fac;
+  a.ab1 = (c->nstep == 0) ? 1 : 0;
+  a.fs = c->p.free_slip & 3;
+  a.sp = g.sp;
+  PSMS_TRY(psms::launch_chan_tau(a, nc, st));
 #undef PSMS_TRY
   return hipSuccess;
 }
@@ -1957,9 +1867,9 @@ int psms_channel_create(psms_channel** out, const psms_channel_params* p, void* 
   c->coef.beta = 2.0 * p->re / p->dt;
   c->coef.dt = p->dt;
   c->coef.forcing = p->forcing;
-  c->coef.ab1 = 1;
   c->nstep = 0;
   c->have_state = 0;
+  c->d_valid = 0;
   // line wavenumbers (kx = 2 pi m / lx, ky = 2 pi m / ly over the band) and twiddles
   const psms::ChanGeom& g = c->g;
   std::vector<double> hkx(g.NL), hky(g.NL);
@@ -2001,56 +1911,11 @@ int psms_channel_create(psms_channel** out, const psms_channel_params* p, void* 
   if (e == hipSuccess) e = hipMemcpyAsync(c->ws + lay.twy32, y32.data(), y32.size() * sizeof(cpx<float>), hipMemcpyHostToDevice, st);
   if (e == hipSuccess) e = hipMemcpyAsync(c->ws + lay.twz64, z64.data(), z64.size() * sizeof(cpx<double>), hipMemcpyHostToDevice, st);
   if (e == hipSuccess) e = hipMemcpyAsync(c->ws + lay.twz32, z32.data(), z32.size() * sizeof(cpx<float>), hipMemcpyHostToDevice, st);
-  // homogeneous solutions of the clamped w problem (unit psi at one wall) and
-  // their influence matrix: fixed for the context (k^2 and beta are)
-  if (e == hipSuccess) {
-    const cpx<double> z0 = {0.0, 0.0}, one = {1.0, 0.0};
-    const double* kx = c->at<double>(lay.kx);
-    const double* ky = c->at<double>(lay.ky);
-    cpx<double>* pt = c->at<cpx<double>>(lay.psip);
-    cpx<double>* pb = c->at<cpx<double>>(lay.xi);
-    double* xw = c->at<double>(lay.xw);
-    const long long xws = (long long)(p->nc + 1) * g.NL;
-    psms::HelmBatch b{};
-    b.np = 2;
-    b.p[0] = psms::HelmProblem{nullptr, pt, xw, g.NL, c->coef.beta, kx, ky, 0, one, z0};
-    b.p[1] = psms::HelmProblem{nullptr, pb, xw + xws, g.NL, c->coef.beta, kx, ky, 0, z0, one};
-    e = psms::launch_helm_batch(b, p->nc, st);
-    if (e == hipSuccess) {
-      b.p[0] = psms::HelmProblem{pt, c->at<cpx<double>>(lay.wt), xw, g.NL, 0.0, kx, ky, 0, z0, z0};
-      b.p[1] = psms::HelmProblem{pb, c->at<cpx<double>>(lay.wb), xw + xws, g.NL, 0.0, kx, ky, 0, z0, z0};
-      e = psms::launch_helm_batch(b, p->nc, st);
-    }
-    if (e == hipSuccess)
-      e = psms::launch_influence_pre(c->at<cpx<double>>(lay.wt), c->at<cpx<double>>(lay.wb), p->nc, g.NL,
-                                     c->at<double>(lay.M), p->free_slip & 3, st);
-    if (e == hipSuccess)
-      e = psms::launch_influence_parity_pre(c->at<cpx<double>>(lay.wt), c->at<cpx<double>>(lay.wb), p->nc, g.NL,
-                                            c->at<double>(lay.whp), c->at<double>(lay.mhp), st);
-    // elimination factors of the step's tau problems (their beta + k^2 and
-    // wall conditions are fixed for the context)
-    if (e == hipSuccess && lay.has_fac) {
-      const int fs = p->free_slip & 3;
-      const size_t fd = psms::helm_factor_doubles(p->nc, g.NL);
-      double* fac = c->at<double>(lay.fac);
-      auto prob = [&](double beta, bool lines, int bc) {
-        psms::HelmProblem h{};
-        h.nlines = lines ? g.NL : 2;
-        h.beta_add = beta;
-        h.kx = lines ? kx : nullptr;
-        h.ky = lines ? ky : nullptr;
-        h.bc = bc;
-        return h;
-      };
-      const psms::HelmProblem probs[kChanFacCount] = {prob(c->coef.beta, true, fs), prob(c->coef.beta, true, 0),
-                                                     prob(c->coef.beta, false, fs), prob(c->a_fac, true, 3),
-                                                     prob(0.0, true, 0), prob(c->b_fac, true, 3)};
-      for (int k = 0; k < kChanFacCount && e == hipSuccess; ++k) {
-        if (g.sp && (k == kChanFacXi || k == kChanFacPhi)) continue;   // no phi equation
-        e = psms::launch_helm_factors(probs[k], p->nc, fac + k * fd, st);
-      }
-    }
-  }
+  // homogeneous solutions of the clamped w problem: fixed for the context (k^2
+  // and beta are)
+  if (e == hipSuccess)
+    e = psms::launch_tau_hom(c->coef.beta, c->at<double>(lay.kx), c->at<double>(lay.ky), p->nc, g.NL,
+                             c->at<double>(lay.whp), c->at<double>(lay.mhp), st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   if (e != hipSuccess) {
     delete c;
@@ -2075,7 +1940,10 @@ int psms_channel_init_state(psms_channel* c, const double* d_u, const double* d_
   const int nf = g.sp ? 3 : 4;
   for (int f = 0; f < nf && e == hipSuccess; ++f)
     e = hipMemcpyAsync(C + f * g.P, src[f], size_t(g.P) * sizeof(double), hipMemcpyDeviceToDevice, c->stream);
-  if (e == hipSuccess) e = chan_forward<double>(c, C, A, nf);
+  if (e == hipSuccess) e = chan_forward_xy<double>(c, C, nf);
+  if (e == hipSuccess)
+    e = psms::launch_dct_fields<double>(g.nc, c->at<cpx<double>>(L.A2), A, g.NL, g.NZL, nf, chan_twz<double>(c), +1,
+                                        c->stream);
   if (e == hipSuccess)
     e = psms::launch_ch_init(g, A, c->at<double>(L.kx), c->at<double>(L.ky), c->at<cpx<double>>(L.state),
                              c->at<cpx<double>>(L.state) + g.NZL, c->at<cpx<double>>(L.state) + 2 * g.NZL,
@@ -2088,6 +1956,7 @@ int psms_channel_init_state(psms_channel* c, const double* d_u, const double* d_
   if (e != hipSuccess) return hip_fail(e, "channel_init_state");
   c->nstep = 0;
   c->have_state = 1;
+  c->d_valid = 0;
   // a non-finite input value reaches every coefficient of its line through the
   // transforms: the diagnostics' count finds it
   psms_diag d;
@@ -2117,17 +1986,10 @@ int psms_channel_diagnostics(psms_channel* c, psms_diag* h_out) {
   double* out = part2 + 4 * kChanDiagBlocks;
   const int nb1 = int(std::min<long long>(kChanDiagBlocks, (g.NL + 3) / 4));
   const int nb2 = int(std::min<long long>(kChanDiagBlocks, (g.P + 255) / 256));
-  // D w and D phi (the step's scratch: the next step recomputes them), the
-  // per-line sums, then u, v, w in FP64 on the collocation grid for the CFL
+  // D w and D phi, the per-line sums, then u, v, w in FP64 on the collocation grid for the CFL
   // number (through the step's transform buffers, which hold 4 FP64 fields in
   // MIXED)
-  psms::ChebBatch cb{};
-  cb.n = g.sp ? 1 : 2;
-  cb.in[0] = w;
-  cb.out[0] = C64(L.dw);
-  cb.in[1] = phi;
-  cb.out[1] = C64(L.dphi);
-  hipError_t e = psms::launch_cheb_batch(cb, g.nc, g.NL, kx, ky, 0, st);
+  hipError_t e = c->d_valid ? hipSuccess : chan_derivatives(c);
   if (e == hipSuccess)
     e = psms::launch_ch_diag_lines(g, om, w, phi, C64(L.dw), C64(L.dphi), C64(L.mean), kx, ky, part, nb1, st);
   if (e == hipSuccess)
@@ -2185,6 +2047,7 @@ int psms_channel_set_state(psms_channel* c, const double* d_state, const double*
   if (e != hipSuccess) return hip_fail(e, "channel_set_state");
   c->nstep = nstep;
   c->have_state = 1;
+  c->d_valid = 0;
   return PSMS_OK;
 }
 
@@ -2193,6 +2056,10 @@ int psms_channel_step(psms_channel* c, int32_t nsteps) {
   if (nsteps < 0) return fail(PSMS_E_INVAL, "nsteps must be >= 0");
   if (!c->have_state) return fail(PSMS_E_STATE, "step before init_state / set_state");
   const bool mixed = c->p.precision == PSMS_MIXED;
+  if (nsteps > 0 && !c->d_valid) {
+    const hipError_t e = chan_derivatives(c);
+    if (e != hipSuccess) return hip_fail(e, "channel_step");
+  }
   for (int i = 0; i < nsteps; ++i) {
     // after the Adams-Bashforth 1 step every step is the same launch sequence
     // with the same arguments: capture it once and replay it
@@ -2213,7 +2080,10 @@ int psms_channel_step(psms_channel* c, int32_t nsteps) {
     } else {
       e = mixed ? chan_step_once<float>(c) : chan_step_once<double>(c);
     }
-    if (e != hipSuccess) return hip_fail(e, "channel_step");
+    if (e != hipSuccess) {
+      c->d_valid = 0;
+      return hip_fail(e, "channel_step");
+    }
     ++c->nstep;
   }
   return PSMS_OK;

@@ -1,9 +1,9 @@
 // Pointwise and per-mode kernels of the channel step (Sec. 2.2): the fields to
-// transform, the products, and the assembly of the wall-normal right-hand
-// sides.  The transforms themselves (Fourier lines and rows, the DCT-I) and
-// the wall-normal solves are the kernels of box_kernels.hip and
-// channel_kernels.hip; every kernel here is one grid-stride pass over
-// contiguous arrays (HBM-bound).
+// transform, the products, the initial state, the diagnostics.  The transforms
+// themselves (Fourier lines and rows, the DCT-I) are the kernels of
+// box_kernels.hip and channel_kernels.hip, the wall-normal right-hand sides and
+// solves those of channel_tau.hip; every kernel here is one grid-stride pass
+// over contiguous arrays (HBM-bound).
 #include <hip/hip_runtime.h>
 
 #include "channel_step_kernels.hpp"
@@ -91,50 +91,6 @@ __global__ void k_ch_products(ChanGeom g, T* __restrict__ f, T cs) {
     f[5 * g.P + id] = -v * w - cs * gy * gz;            // T_yz
     f[6 * g.P + id] = u * gx + v * gy + w * gz;         // u . grad phi
     f[7 * g.P + id] = p * p * p;                        // phi^3
-  }
-}
-
-__device__ __forceinline__ cpx<double> ab(cpx<double> h, cpx<double> hp, int ab1) {
-  return ab1 ? h : cpx<double>{1.5 * h.re - 0.5 * hp.re, 1.5 * h.im - 0.5 * hp.im};
-}
-
-__global__ void k_ch_assemble(ChanGeom g, ChanCoef c, ChanAssembleArgs a) {
-  PSMS_GRID_LOOP(id, g.NZL) {
-    const long long l = id % g.NL, n = id / g.NL;
-    const double kx = a.kx[l], ky = a.ky[l];
-    const double k2 = kx * kx + ky * ky;
-    // S = div T: S_x = i kx T_xx + i ky T_xy + D T_xz, and likewise
-    const cpx<double> txx = a.R[id], tyy = a.R[g.NZL + id], txy = a.R[3 * g.NZL + id];
-    const cpx<double> txz = a.R[4 * g.NZL + id], tyz = a.R[5 * g.NZL + id];
-    const cpx<double> sx = add(add(ti(kx, txx), ti(ky, txy)), a.d3[id]);
-    const cpx<double> sy = add(add(ti(kx, txy), ti(ky, tyy)), a.d3[g.NZL + id]);
-    const cpx<double> sz = add(add(ti(kx, txz), ti(ky, tyz)), a.d3[2 * g.NZL + id]);
-    const cpx<double> h_om = sub(ti(kx, sy), ti(ky, sx));                    // (curl S)_z
-    const cpx<double> h_w = sub(scl(-k2, sz), a.dq[id]);                     // lap_h S_z - D(div_h S)
-    const cpx<double> e_om = ab(h_om, a.hist[id], c.ab1);
-    const cpx<double> e_w = ab(h_w, a.hist[g.NZL + id], c.ab1);
-    a.hist[id] = h_om;
-    a.hist[g.NZL + id] = h_w;
-    const double r2 = 2.0 * c.re;
-    a.g[id] = sub(scl(-1.0, a.lom[id]), scl(r2, e_om));        // -(lap + beta) omega - 2 Re E
-    a.g[g.NZL + id] = sub(scl(-1.0, a.lpsi[id]), scl(r2, e_w));
-    if (!g.sp) {
-      const cpx<double> s_phi = sub(a.lsphi[id], a.R[6 * g.NZL + id]);  // -a + lap c / Pe - (1 + s Ch^2)/Pe lap phi
-      const cpx<double> e_phi = ab(s_phi, a.hist[2 * g.NZL + id], c.ab1);
-      a.hist[2 * g.NZL + id] = s_phi;
-      a.g[2 * g.NZL + id] = scl(c.g_phi_scale, add(a.phi[id], scl(c.dt, e_phi)));
-    }
-    if (l == 0) {  // mean flow: S_x, S_y of the mean line, driving -dP/dx = forcing on T_0
-#pragma unroll
-      for (int k = 0; k < 2; ++k) {
-        const cpx<double> h = k ? sy : sx;
-        cpx<double> e = ab(h, a.hmean[2 * n + k], c.ab1);
-        a.hmean[2 * n + k] = h;
-        if (k == 0 && n == 0) e.re += c.forcing;
-        const cpx<double> U = a.mean[2 * n + k];
-        a.gmean[2 * n + k] = sub(scl(-1.0, add(a.d2mean[2 * n + k], scl(c.beta, U))), scl(r2, e));
-      }
-    }
   }
 }
 
@@ -401,10 +357,6 @@ hipError_t launch_ch_fields(const ChanGeom& g, const cpx<double>* om, const cpx<
 template <typename T>
 hipError_t launch_ch_products(const ChanGeom& g, T* f, double csig, hipStream_t st) {
   k_ch_products<T><<<blocks_for(g.P), kThreads, 0, st>>>(g, f, T(csig));
-  return hipGetLastError();
-}
-hipError_t launch_ch_assemble(const ChanGeom& g, const ChanCoef& c, const ChanAssembleArgs& a, hipStream_t st) {
-  k_ch_assemble<<<blocks_for(g.NZL), kThreads, 0, st>>>(g, c, a);
   return hipGetLastError();
 }
 hipError_t launch_ch_init(const ChanGeom& g, const cpx<double>* U4, const double* kx, const double* ky,

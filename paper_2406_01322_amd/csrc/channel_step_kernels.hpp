@@ -25,7 +25,6 @@ struct ChanCoef {
   double re, beta;     // Re_tau and 2 Re / dt
   double inv_pe, e_coef, g_phi_scale, dt, forcing;
   double csig;
-  int ab1;
 };
 
 // the 7 spectral fields u, v, w, phi, i kx phi, i ky phi, D phi (precision T);
@@ -39,27 +38,6 @@ hipError_t launch_ch_fields(const ChanGeom& g, const cpx<double>* om, const cpx<
 // phase 3 in, the 6 components of -u_i u_j out
 template <typename T>
 hipError_t launch_ch_products(const ChanGeom& g, T* f, double csig, hipStream_t st);
-// H_omega, H_w, S_phi; Adams-Bashforth with the history (then overwritten);
-// the right-hand sides g_om, g_w, g_phi of the wall-normal solves; the mean
-// lines' H and right-hand sides.
-struct ChanAssembleArgs {
-  const cpx<double>* d3;      // [3][NZL] D T_xz, D T_yz, D T_zz (S = div T is formed from them and R)
-  const cpx<double>* dq;      // D Q, Q = i kx S_x + i ky S_y
-  const cpx<double>* R;       // products T_xx T_yy T_zz T_xy T_xz T_yz, field 6 = a, 7 = c
-  const cpx<double>* lsphi;   // lap (c / Pe - (1 + s Ch^2) / Pe phi^n)
-  const cpx<double>* phi;     // phi^n
-  const cpx<double>* lom;     // lap omega^n + beta omega^n
-  const cpx<double>* lpsi;    // lap psi + beta psi, psi = lap w^n
-  const double* kx;
-  const double* ky;
-  cpx<double>* hist;          // [3][NZL] H_omega, H_w, S_phi of the previous step (in/out)
-  cpx<double>* g;             // [3][NZL] g_om, g_w, g_phi
-  const cpx<double>* mean;    // [nc+1][2] U, V
-  const cpx<double>* d2mean;  // [nc+1][2]
-  cpx<double>* hmean;         // [nc+1][2] (in/out)
-  cpx<double>* gmean;         // [nc+1][2]
-};
-hipError_t launch_ch_assemble(const ChanGeom& g, const ChanCoef& c, const ChanAssembleArgs& a, hipStream_t st);
 // initial state from the 4 transformed physical fields u, v, w, phi ([4][NZL], FP64;
 // 3 in single phase, phi set to zero)
 hipError_t launch_ch_init(const ChanGeom& g, const cpx<double>* U4, const double* kx, const double* ky,

@@ -82,3 +82,96 @@ def test_pieced_wall_solve_sizes(nc, nl):
     for key in ("omega", "w", "phi", "u", "v"):
         a, b = _host(got[key]), want[key]
         assert np.all(np.max(np.abs(a - b), axis=0) <= 1e-11 * np.max(np.abs(b), axis=0)), key
+
+
+def _channel_fields(nx, ny, nc, seed):
+    from paper_2406_01322_amd import synth
+    lx, ly = 4.0 * np.pi, 2.0 * np.pi
+    X, Y, Z = synth.channel_grid(nx, ny, nc, lx, ly)
+    rng = np.random.default_rng(seed)
+    up, vp, wp = synth.channel_perturbation(X, Y, Z, lx, ly, rng, min(4, (nx - 1) // 3, (ny - 1) // 3), 1.0)
+    phi = np.tanh(2.0 * np.cos(0.5 * X + rng.uniform(0, 6)) * np.cos(Y) + Z ** 2 * (1.5 - Z ** 2 / 2) - 0.3)
+    return 10.0 * (1.0 - Z ** 2) + up, vp, wp, phi
+
+
+# The wall-normal half of the channel step in one launch: chains shorter than the
+# pieces or with a partly filled last piece, band line counts below, at and above the
+# 64 of a workgroup, each wall combination (with different walls the workgroup holds
+# both parities).  An AB1 and an AB2 step against the oracle: 1e-12 of each field's
+# maximum, as for the other step tests.  (At these coarse time steps the rounding of
+# the explicit terms, which grows as nc^2, passes that bar from nc = 96 on; the
+# longer chains are held to their wall conditions below.)
+@pytest.mark.parametrize("nx,ny,nc,walls,single", [
+    (8, 8, 4, "nn", False), (12, 8, 6, "ff", False), (16, 12, 8, "fn", False), (24, 24, 12, "nf", False),
+    (16, 24, 24, "nn", True), (32, 16, 48, "fn", True), (16, 16, 64, "nf", False)])
+def test_channel_step_sizes_and_walls(nx, ny, nc, walls, single):
+    from oracle import channel_step as cs
+    from paper_2406_01322_amd.psms import Channel
+    kinds = tuple({"n": "noslip", "f": "freeslip"}[c] for c in walls)
+    prm = cs.ChannelParams(nx=nx, ny=ny, nc=nc, re=20.0, we=1.0, ch=0.2, pe=5.0, dt=1e-3, walls=kinds)
+    f = list(_channel_fields(nx, ny, nc, nc))
+    if single:
+        f[3] = np.zeros_like(f[3])
+    c = Channel(nx, ny, nc, prm.re, prm.we, prm.ch, prm.pe, prm.dt, single_phase=single, walls=kinds)
+    c.init_state(*[_dev(x) for x in f])
+    st = cs.init_state(*f, prm)
+    for _ in range(2):
+        c.step(1)
+        st = cs.step(st, prm)
+        got, mean = (_host(x) for x in c.get_state())
+        for a, b in ((got[0], st["om"]), (got[1], st["w"]), (got[2], st["phi"]), (mean, st["mean"])):
+            assert np.max(np.abs(a - b)) <= 1e-12 * max(np.max(np.abs(b)), 1e-300)
+
+
+# The boundary rows of the solutions for the longer chains (17 slots a piece at nc =
+# 256), to the bars that the wall-solve tests hold them to: 1e-12 of the field's
+# maximum for a value at a wall, 1e-9 for a slope (weights n^2).
+@pytest.mark.parametrize("nc", [96, 128, 256])
+@pytest.mark.parametrize("walls", ["nn", "fn", "nf", "ff"])
+def test_channel_step_wall_conditions(nc, walls):
+    from paper_2406_01322_amd.psms import Channel
+    kinds = tuple({"n": "noslip", "f": "freeslip"}[c] for c in walls)
+    c = Channel(24, 16, nc, 150.0, 3.0, 0.1, 10.0, 1e-4, walls=kinds)
+    c.init_state(*[_dev(x) for x in _channel_fields(24, 16, nc, nc)])
+    c.step(2)
+    (om, w, phi), mean = (_host(x) for x in c.get_state())
+    n = np.arange(nc + 1.0)
+    sign = (-1.0) ** n
+    value = {"t": np.ones(nc + 1), "b": sign}
+    slope = {"t": n * n, "b": -sign * n * n}
+
+    def zero(rows, side, a):
+        a = a.reshape(nc + 1, -1)
+        assert np.all(np.isfinite(a))
+        assert np.max(np.abs(rows[side] @ a)) <= (1e-12 if rows is value else 1e-9) * np.max(np.abs(a))
+
+    for j, side in enumerate("tb"):
+        for a in (om, mean.T):
+            zero(value if walls[j] == "n" else slope, side, a)
+        zero(value, side, w)
+        if walls[j] == "n":
+            zero(slope, side, w)
+        zero(slope, side, phi)
+
+
+# D w and D phi of the state stay in the workspace between steps: a state that is set
+# later, or diagnostics in between, must not meet those of another state.
+def test_channel_derivatives_follow_the_state():
+    from paper_2406_01322_amd.psms import Channel
+    args = (16, 12, 16, 20.0, 1.0, 0.2, 5.0, 1e-3)
+    a, b, c = (Channel(*args) for _ in range(3))
+    f = [[_dev(x) for x in _channel_fields(16, 12, 16, s)] for s in (1, 2)]
+    a.init_state(*f[0])
+    a.step(2)
+    saved = [t.clone() for t in a.get_state(with_history=True)]
+    a.step(1)
+    want = a.get_state()
+    b.init_state(*f[1])
+    b.step(3)
+    b.set_state(*saved, nstep=2)      # another state over a context that has stepped
+    b.step(1)
+    c.set_state(*saved, nstep=2)
+    c.diagnostics()
+    c.step(1)
+    for x in (b, c):
+        assert all(torch.equal(p, q) for p, q in zip(x.get_state(), want))

@@ -1536,7 +1536,7 @@ namespace {
 struct ChanLayout {
   size_t kx, ky, twx64, twx32, twy64, twy32, twz64, twz32;
   size_t state, mean, hist, hmean;
-  size_t dw, dphi, A, A2, B, C, R, whp, mhp, diag, xdev, total;
+  size_t dw, dphi, A2, B, C, R, whp, mhp, diag, xdev, total;
 };
 
 constexpr int kChanDiagBlocks = 1024;   // partial sums of the diagnostics
@@ -1555,8 +1555,6 @@ psms::ChanGeom chan_geom(const psms_channel_params& p) {
   g.NZL = (long long)(p.nc + 1) * g.NL;
   g.P = (long long)(p.nc + 1) * p.ny * p.nx;
   g.sp = p.single_phase ? 1 : 0;
-  g.nf_in = g.sp ? 3 : 7;
-  g.nf_out = g.sp ? 6 : 8;
   return g;
 }
 
@@ -1587,7 +1585,6 @@ ChanLayout chan_layout(const psms_channel_params& p) {
   take(L.hmean, 2 * nz * c64);
   take(L.dw, arr);
   take(L.dphi, arr);
-  take(L.A, 8 * size_t(g.NZL) * t);
   take(L.A2, 8 * size_t(g.NZL) * t);
   take(L.B, 8 * nz * size_t(p.ny) * size_t(g.Hx) * t);
   take(L.C, 8 * size_t(g.P) * tr);
@@ -1692,15 +1689,15 @@ hipError_t chan_forward_xy(psms_channel* c, const T* phys, int nf) {
 
 // band [nf][n][line] (T) -> x-spectral [nf][z][y][kx band] (T) in the buffer B:
 // DCT-I, y lines
-// band [nf][n][line] (T; or, with fs, the step's six fields formed from the
-// state as the transform loads them) -> y-expanded [nf][z][y][x-band] (T)
+// band [nf][n][line] (T; or, with fs, the step's fields formed from the state as
+// the transform loads them) -> y-expanded [nf][z][y][x-band] (T)
 template <typename T>
 hipError_t chan_inverse_yz(psms_channel* c, const cpx<T>* band, int nf, const psms::ChanFieldSrc* fs = nullptr) {
   const psms::ChanGeom& g = c->g;
   const long long nz = g.nc + 1;
   cpx<T>* B = c->at<cpx<T>>(c->lay.B);
   cpx<T>* A2 = c->at<cpx<T>>(c->lay.A2);
-  hipError_t e = fs ? psms::launch_dct_chfields<T>(g.nc, *fs, A2, g.NZL, chan_twz<T>(c), c->stream)
+  hipError_t e = fs ? psms::launch_dct_chfields<T>(g.nc, *fs, A2, g.NZL, nf, chan_twz<T>(c), c->stream)
                     : psms::launch_dct_fields<T>(g.nc, band, A2, g.NL, g.NZL, nf, chan_twz<T>(c), -1, c->stream);
   if (e != hipSuccess) return e;
   psms::LineArgs la{};
@@ -1762,24 +1759,16 @@ hipError_t chan_step_once(psms_channel* c) {
   hipError_t e;
 #define PSMS_TRY(x) \
   if ((e = (x)) != hipSuccess) return e
-  if (g.sp) {
-    PSMS_TRY(psms::launch_ch_fields<T>(g, om, w, phi, C64(L.dw), C64(L.dphi), C64(L.mean), kx, ky,
-                                       c->at<cpx<T>>(L.A), st));
-    PSMS_TRY(chan_inverse<T>(c, c->at<cpx<T>>(L.A), c->at<T>(L.C), g.nf_in));
-    PSMS_TRY(psms::launch_ch_products<T>(g, c->at<T>(L.C), c->coef.csig, st));
-    PSMS_TRY(chan_forward_xy<T>(c, c->at<T>(L.C), g.nf_out));
-  } else {
-    // two-phase: u, v, w, phi, dy phi, dz phi through the DCT-I (each formed from
-    // the state as the transform loads it) and y lines; the x-inverse, the 8
-    // products and the x-forward in one pass (the box's x stage on (nc + 1) ny
-    // rows; dx phi formed on load), so that no physical field is stored; then y
-    // lines
-    const psms::ChanFieldSrc fs{om, w, phi, C64(L.dw), C64(L.dphi), C64(L.mean), kx, ky, nl};
-    PSMS_TRY(chan_inverse_yz<T>(c, nullptr, 6, &fs));
-    PSMS_TRY(psms::launch_xstage_rows<T>(g.nx, c->at<psms::BoxDev>(L.xdev), chan_tw<T>(c, true),
-                                         (long long)(nc + 1) * g.ny, 2.0 * M_PI / c->p.lx, st));
-    PSMS_TRY(chan_forward_y<T>(c, c->at<cpx<T>>(L.C), 8));
-  }
+  // u, v, w (two-phase: phi, dy phi, dz phi) through the DCT-I (each formed from
+  // the state as the transform loads it) and y lines; the x-inverse, the 8 (6)
+  // products and the x-forward in one pass (the box's x stage on (nc + 1) ny
+  // rows; dx phi formed on load), so that no physical field is stored; then y
+  // lines
+  const psms::ChanFieldSrc fs{om, w, phi, C64(L.dw), C64(L.dphi), C64(L.mean), kx, ky, nl};
+  PSMS_TRY(chan_inverse_yz<T>(c, nullptr, g.sp ? 3 : 6, &fs));
+  PSMS_TRY(psms::launch_xstage_rows<T>(g.nx, c->at<psms::BoxDev>(L.xdev), chan_tw<T>(c, true),
+                                       (long long)(nc + 1) * g.ny, 2.0 * M_PI / c->p.lx, g.sp != 0, st));
+  PSMS_TRY(chan_forward_y<T>(c, c->at<cpx<T>>(L.C), g.sp ? 6 : 8));
   // the products' combinations through the DCT-I with the Chebyshev cut (FP64),
   // then everything wall-normal in one launch
   PSMS_TRY(psms::launch_dct_chterms<T>(nc, c->at<cpx<T>>(L.A2), C64(L.R), nl, g.NZL, g.sp ? 4 : 6, kx, ky,
@@ -1993,7 +1982,7 @@ int psms_channel_diagnostics(psms_channel* c, psms_diag* h_out) {
   if (e == hipSuccess)
     e = psms::launch_ch_diag_lines(g, om, w, phi, C64(L.dw), C64(L.dphi), C64(L.mean), kx, ky, part, nb1, st);
   if (e == hipSuccess)
-    e = psms::launch_ch_fields<double>(g, om, w, phi, C64(L.dw), C64(L.dphi), C64(L.mean), kx, ky, C64(L.R), st);
+    e = psms::launch_ch_uvw(g, om, w, C64(L.dw), C64(L.mean), kx, ky, C64(L.R), st);
   if (e == hipSuccess) e = chan_inverse<double>(c, C64(L.R), c->at<double>(L.C), 3);
   if (e == hipSuccess)
     e = psms::launch_ch_cfl(g, c->at<double>(L.C), g.nx / c->p.lx, g.ny / c->p.ly, c->p.dt, part2, nb2, st);

@@ -338,13 +338,28 @@ __device__ __forceinline__ T xproduct(const cpx<T> (&ph)[7][E], int e, int c, T 
   else return p3 * p3 * p3;                                               // phi^3
 }
 
-// order in which the x stage forms and transforms the 8 products
-constexpr int kXstepFwdOrder[8] = {7, 6, 0, 1, 2, 3, 4, 5};
+// the same in single phase: -u_i u_j of the 3 fields u, v, w
+template <int F, typename T, int E>
+__device__ __forceinline__ T xproduct(const cpx<T> (&ph)[3][E], int e, int c, T) {
+  constexpr int i = F < 3 ? F : F == 5 ? 1 : 0, j = F < 3 ? F : F == 3 ? 1 : 2;
+  const T a = c ? ph[i][e].im : ph[i][e].re, b = c ? ph[j][e].im : ph[j][e].re;
+  return -a * b;
+}
+
+// order in which the x stage forms and transforms the products
+template <bool SP>
+constexpr int xstep_fwd_order(int f) {
+  constexpr int two_phase[8] = {7, 6, 0, 1, 2, 3, 4, 5};
+  return SP ? f : two_phase[f];
+}
 
 // CH: the same stage on rows of any count (the plane channel's x stage:
 // xrows = (nc + 1) ny rows of the y-inverse, kx = kxs k for x periods other
-// than 2 pi); the box passes xrows = N^2 and kxs = 1 implicitly.
-template <typename T, int N, int V, bool CH = false>
+// than 2 pi); the box passes xrows = N^2 and kxs = 1 implicitly.  SP: single
+// phase, 3 fields in and 6 products out; bound by memory: 255 us at 256 x 256 x
+// 257 in FP64, where x-inverse, products and x-forward as passes of their own,
+// with the physical fields stored between them, took 760 us.
+template <typename T, int N, int V, bool CH = false, bool SP = false>
 __global__ void __launch_bounds__(64 << V) __attribute__((amdgpu_waves_per_eu(kXstepWaves<T, N>)))
 k_xstep(const BoxDev* __restrict__ boxes, int box0, const cpx<T>* __restrict__ tw_g, long long xrows, double kxs) {
   using P = Plan<N>;
@@ -356,7 +371,8 @@ k_xstep(const BoxDev* __restrict__ boxes, int box0, const cpx<T>* __restrict__ t
   constexpr bool WIDE = kXstepWide<T, N>;
   constexpr bool SWZ = kXstepSwz<T, N>;
   constexpr int E = G::E, TT = G::TT, L = G::L, LP = SWZ ? kRowStrideSwz<N> : kRowStride<N>, K = G::K, H = G::H;
-  constexpr int NFF = WIDE ? 4 : 2;   // products per forward group
+  constexpr int NV = SP ? 3 : 7, NPR = SP ? 6 : 8;   // fields, products
+  constexpr int NFF = !WIDE ? 2 : SP ? 3 : 4;        // products per forward group
   constexpr int RI = first_radix<P, 1>();   // inverse starts with R[NST-1]
   constexpr int RP = last_radix<P, 1>();    // inverse ends / forward starts with R[0]
   constexpr int RO = last_radix<P, -1>();   // forward ends with R[NST-1]
@@ -382,7 +398,7 @@ k_xstep(const BoxDev* __restrict__ boxes, int box0, const cpx<T>* __restrict__ t
   // registers allow (PF), the loads of the next pair are issued before the
   // current pair is transformed, so that their latency overlaps the transforms;
   // under the four-wavefront register budget they would spill.
-  cpx<T> ph[7][E];
+  cpx<T> ph[NV][E];
   // raw retained kx of both rows of field vf at slot e (= b RI + r) of the
   // positions the inverse starts from
   auto load_raw_slot = [&](int vf, int e, cpx<T>& A, cpx<T>& B) {
@@ -435,7 +451,7 @@ k_xstep(const BoxDev* __restrict__ boxes, int box0, const cpx<T>* __restrict__ t
 #pragma unroll
     for (int g = 0; g < 2; ++g) {
       const int vf = vf0 + g;
-      if (vf >= 7) continue;
+      if (vf >= NV) continue;
       const int fin = (vf <= 3) ? vf : vf - 1;
       const char* src = reinterpret_cast<const char*>(yin + (long long)fin * ROWS * H + (long long)wrow0 * H);
       const long long left = (ROWS - wrow0) * H * (long long)sizeof(cpx<T>);   // bytes of the field from here
@@ -451,9 +467,9 @@ k_xstep(const BoxDev* __restrict__ boxes, int box0, const cpx<T>* __restrict__ t
   }
   if constexpr (WIDE) {
     // four inverse transforms per LDS round trip: fields 0-3, then 4-6
-    static_for<0, 2>([&](auto gi) {
+    static_for<0, SP ? 1 : 2>([&](auto gi) {
       constexpr int f0 = decltype(gi)::value * 4;
-      constexpr int nf = f0 == 0 ? 4 : 3;
+      constexpr int nf = f0 == 0 && !SP ? 4 : 3;
       cpx<T> v[nf][E];
 #pragma unroll
       for (int g = 0; g < nf; ++g)
@@ -471,8 +487,8 @@ k_xstep(const BoxDev* __restrict__ boxes, int box0, const cpx<T>* __restrict__ t
     });
   } else
 #pragma unroll
-  for (int vf = 0; vf < 7; vf += 2) {
-    const int nf = (vf + 1 < 7) ? 2 : 1;
+  for (int vf = 0; vf < NV; vf += 2) {
+    const int nf = (vf + 1 < NV) ? 2 : 1;
     cpx<T> v[2][E];
     if (XDMA) {
       xstage_wait();
@@ -493,14 +509,14 @@ k_xstep(const BoxDev* __restrict__ boxes, int box0, const cpx<T>* __restrict__ t
           }
         }
       xstage_release();
-      if (vf + 2 < 7) dma_pair(vf + 2);
+      if (vf + 2 < NV) dma_pair(vf + 2);
     } else if (PF) {
 #pragma unroll
       for (int g = 0; g < 2; ++g)
         if (g < nf) pack(vf + g, ra[g], rb[g], v[g]);
 #pragma unroll
       for (int g = 0; g < 2; ++g)
-        if (vf + 2 + g < 7) load_raw(vf + 2 + g, ra[g], rb[g]);
+        if (vf + 2 + g < NV) load_raw(vf + 2 + g, ra[g], rb[g]);
     } else {
       // load and pack slot by slot, so that few raw values are live at once
 #pragma unroll
@@ -534,12 +550,12 @@ k_xstep(const BoxDev* __restrict__ boxes, int box0, const cpx<T>* __restrict__ t
   const T cs = T(csig_d);
   const T h = T(0.5);
   static_assert(RP == first_radix<P, -1>(), "mirrored radix order");
-  static_for<0, 8 / NFF>([&](auto gi) {
+  static_for<0, NPR / NFF>([&](auto gi) {
     constexpr int f0 = decltype(gi)::value * NFF;
     cpx<T> v[NFF][E];
     static_for<0, NFF>([&](auto gc) {
       constexpr int g = decltype(gc)::value;
-      constexpr int F = kXstepFwdOrder[f0 + g];
+      constexpr int F = xstep_fwd_order<SP>(f0 + g);
 #pragma unroll
       for (int e = 0; e < E; ++e) v[g][e] = cpx<T>{xproduct<F>(ph, e, 0, cs), xproduct<F>(ph, e, 1, cs)};
     });
@@ -554,7 +570,7 @@ k_xstep(const BoxDev* __restrict__ boxes, int box0, const cpx<T>* __restrict__ t
     wave_lds_sync();  // the line's threads are one wavefront's lanes
     static_for<0, NFF>([&](auto gc) {
       constexpr int g = decltype(gc)::value;
-      cpx<T>* dst = xout + (long long)kXstepFwdOrder[f0 + g] * ROWS * H;
+      cpx<T>* dst = xout + (long long)xstep_fwd_order<SP>(f0 + g) * ROWS * H;
       for (int k = t; valid && k < H; k += TT) {
         const cpx<T> zk = lds[g][idx(k)];
         const cpx<T> zm = lds[g][idx((N - k) % N)];
@@ -1163,21 +1179,22 @@ hipError_t step_n(int stage, int variant, const BoxDev* boxes, int box0, int nbo
 }  // namespace
 
 template <typename T, int N>
-hipError_t xstage_rows_n(const BoxDev* dev, const cpx<T>* tw, long long rows, double kxs, hipStream_t st) {
+hipError_t xstage_rows_n(const BoxDev* dev, const cpx<T>* tw, long long rows, double kxs, bool sp, hipStream_t st) {
   using G = Tile<Plan<N>, 2>;
   const long long pairs = rows / 2;
   const dim3 grid(unsigned((pairs + G::L - 1) / G::L), 1, 1);
-  k_xstep<T, N, 2, true><<<grid, unsigned(G::L * G::TT), 0, st>>>(dev, 0, tw, rows, kxs);
+  if (sp) k_xstep<T, N, 2, true, true><<<grid, unsigned(G::L * G::TT), 0, st>>>(dev, 0, tw, rows, kxs);
+  else k_xstep<T, N, 2, true><<<grid, unsigned(G::L * G::TT), 0, st>>>(dev, 0, tw, rows, kxs);
   return hipGetLastError();
 }
 
 template <typename T>
-hipError_t launch_xstage_rows(int n, const BoxDev* dev, const cpx<T>* tw, long long rows, double kxs,
+hipError_t launch_xstage_rows(int n, const BoxDev* dev, const cpx<T>* tw, long long rows, double kxs, bool sp,
                               hipStream_t st) {
   if (rows <= 0) return hipSuccess;
   if (rows % 2) return hipErrorInvalidValue;   // rows are transformed in pairs
   switch (n) {
-#define PSMS_CASE(NN) case NN: return xstage_rows_n<T, NN>(dev, tw, rows, kxs, st);
+#define PSMS_CASE(NN) case NN: return xstage_rows_n<T, NN>(dev, tw, rows, kxs, sp, st);
     PSMS_FOR_EACH_N(PSMS_CASE)
 #undef PSMS_CASE
   }
@@ -1309,7 +1326,8 @@ template hipError_t launch_compact<double>(const cpx<double>*, cpx<double>*, con
 using PartT = float;
 template hipError_t launch_band_to<float>(const cpx<double>*, cpx<float>*, long long, hipStream_t);
 #endif
-template hipError_t launch_xstage_rows<PartT>(int, const BoxDev*, const cpx<PartT>*, long long, double, hipStream_t);
+template hipError_t launch_xstage_rows<PartT>(int, const BoxDev*, const cpx<PartT>*, long long, double, bool,
+                                              hipStream_t);
 template hipError_t launch_cube<PartT>(PartT*, long long, hipStream_t);
 template hipError_t launch_pressure_band<PartT>(const cpx<PartT>*, const BoxGeom&, cpx<double>*, hipStream_t);
 template hipError_t launch_lines<PartT>(int, int, const cpx<PartT>*, cpx<PartT>*, const cpx<PartT>*, const LineArgs&,

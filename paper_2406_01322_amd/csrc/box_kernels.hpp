@@ -80,9 +80,10 @@ hipError_t launch_step_stage(int n, int stage, int variant, const BoxDev* table,
 // load from phi), dy phi, dz phi; the 8 products; x-forward) on `rows` rows
 // of length n (rows even): dev->bufa holds the 6 input fields [6][rows][n/2+1
 // band entries K+1], dev->bufb receives the 8 products [8][rows][K+1]; kx =
-// kxs k; dev->csig the capillary coefficient.  One descriptor (box0 = 0).
+// kxs k; dev->csig the capillary coefficient.  One descriptor (box0 = 0).  sp:
+// u, v, w in ([3][rows][K+1]) and the six -u_i u_j out.
 template <typename T>
-hipError_t launch_xstage_rows(int n, const BoxDev* dev, const cpx<T>* tw, long long rows, double kxs,
+hipError_t launch_xstage_rows(int n, const BoxDev* dev, const cpx<T>* tw, long long rows, double kxs, bool sp,
                               hipStream_t st);
 // field f of a compact band [nf][C][C][H] into the full half spectrum out.p[f]
 constexpr int kSpecOutMax = 8;

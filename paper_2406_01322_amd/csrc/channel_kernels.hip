@@ -704,20 +704,20 @@ hipError_t launch_dct_fields(int nc, const cpx<T>* in, cpx<T>* out, long long nl
 }
 
 template <typename T>
-hipError_t launch_dct_chfields(int nc, const ChanFieldSrc& fs, cpx<T>* out, long long fstride, const cpx<T>* tw,
-                               hipStream_t st) {
+hipError_t launch_dct_chfields(int nc, const ChanFieldSrc& fs, cpx<T>* out, long long fstride, int nfield,
+                               const cpx<T>* tw, hipStream_t st) {
   if (fs.nlines == 0) return hipSuccess;
   const ChanFieldSrcT<T> src{fs};
   switch (2 * nc) {
-#define PSMS_CASE(NN) case NN: return dct_n<T, NN>(src, out, fs.nlines, -1, fstride, 6, tw, nullptr, 0, st);
+#define PSMS_CASE(NN) case NN: return dct_n<T, NN>(src, out, fs.nlines, -1, fstride, nfield, tw, nullptr, 0, st);
     PSMS_FOR_EACH_2NC(PSMS_CASE)
 #undef PSMS_CASE
   }
   return hipErrorInvalidValue;
 }
-template hipError_t launch_dct_chfields<float>(int, const ChanFieldSrc&, cpx<float>*, long long, const cpx<float>*,
-                                               hipStream_t);
-template hipError_t launch_dct_chfields<double>(int, const ChanFieldSrc&, cpx<double>*, long long,
+template hipError_t launch_dct_chfields<float>(int, const ChanFieldSrc&, cpx<float>*, long long, int,
+                                               const cpx<float>*, hipStream_t);
+template hipError_t launch_dct_chfields<double>(int, const ChanFieldSrc&, cpx<double>*, long long, int,
                                                 const cpx<double>*, hipStream_t);
 
 template <typename T>

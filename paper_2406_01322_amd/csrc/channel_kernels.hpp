@@ -23,8 +23,8 @@ hipError_t launch_dct_fields(int nc, const cpx<T>* in, cpx<T>* out, long long nl
 template <typename T>
 hipError_t launch_dct_chterms(int nc, const cpx<T>* in, cpx<double>* out, long long nlines, long long fstride, int nterm,
                               const double* kx, const double* ky, const cpx<T>* tw, int kz, hipStream_t st);
-// The inverse transform of the channel step's six fields u, v, w, phi, i ky phi,
-// D phi ([6][n][line] out, fstride apart), each value formed from the FP64
+// The inverse transform of the channel step's fields u, v, w, phi, i ky phi, D phi
+// (nfield = 6, or 3: u, v, w; [nfield][n][line] out, fstride apart), each value formed from the FP64
 // state as it is loaded (u, v by continuity and the definition of omega_z;
 // the mean line, l = 0, carries U, V from mean [n][2]).
 struct ChanFieldSrc {
@@ -39,8 +39,8 @@ struct ChanFieldSrc {
   long long nlines;
 };
 template <typename T>
-hipError_t launch_dct_chfields(int nc, const ChanFieldSrc& fs, cpx<T>* out, long long fstride, const cpx<T>* tw,
-                               hipStream_t st);
+hipError_t launch_dct_chfields(int nc, const ChanFieldSrc& fs, cpx<T>* out, long long fstride, int nfield,
+                               const cpx<T>* tw, hipStream_t st);
 hipError_t launch_chebd(const cpx<double>* a, cpx<double>* d, int nc, long long nlines, hipStream_t st);
 hipError_t launch_helm(const cpx<double>* g, cpx<double>* f, double* xw, int nc, long long nlines,
                        const double* beta_line, double beta_add, const double* kx, const double* ky, int neumann,

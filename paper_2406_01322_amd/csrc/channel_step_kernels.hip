@@ -1,5 +1,4 @@
-// Pointwise and per-mode kernels of the channel step (Sec. 2.2): the fields to
-// transform, the products, the initial state, the diagnostics.  The transforms
+// Per-mode kernels of the channel (Sec. 2.2): the initial state, the diagnostics.  The transforms
 // themselves (Fourier lines and rows, the DCT-I) are the kernels of
 // box_kernels.hip and channel_kernels.hip, the wall-normal right-hand sides and
 // solves those of channel_tau.hip; every kernel here is one grid-stride pass
@@ -28,69 +27,26 @@ __device__ __forceinline__ cpx<double> scl(double s, cpx<double> a) { return {s 
 #define PSMS_GRID_LOOP(id, n) \
   for (long long id = (long long)blockIdx.x * blockDim.x + threadIdx.x; id < (n); id += (long long)gridDim.x * blockDim.x)
 
-template <typename T>
-__global__ void k_ch_fields(ChanGeom g, const cpx<double>* __restrict__ om, const cpx<double>* __restrict__ w,
-                            const cpx<double>* __restrict__ phi, const cpx<double>* __restrict__ dw,
-                            const cpx<double>* __restrict__ dphi, const cpx<double>* __restrict__ mean,
-                            const double* __restrict__ kxl, const double* __restrict__ kyl, cpx<T>* __restrict__ out,
-                            int six) {
+// u, v (continuity and the definition of omega_z; the mean line carries U, V) and w
+__global__ void k_ch_uvw(ChanGeom g, const cpx<double>* __restrict__ om, const cpx<double>* __restrict__ w,
+                         const cpx<double>* __restrict__ dw, const cpx<double>* __restrict__ mean,
+                         const double* __restrict__ kxl, const double* __restrict__ kyl, cpx<double>* __restrict__ out) {
   PSMS_GRID_LOOP(id, g.NZL) {
     const long long l = id % g.NL, n = id / g.NL;
     const double kx = kxl[l], ky = kyl[l];
     cpx<double> u, v;
-    if (l == 0) {  // the mean line carries U, V
+    if (l == 0) {
       u = mean[2 * n];
       v = mean[2 * n + 1];
-    } else {       // continuity and the definition of omega_z (eq. omegadef)
+    } else {
       const double ik2 = 1.0 / (kx * kx + ky * ky);
       const cpx<double> o = om[id], d = dw[id];
       u = scl(ik2, ti(1.0, add(scl(kx, d), scl(ky, o))));
       v = scl(ik2, ti(1.0, sub(scl(ky, d), scl(kx, o))));
     }
-    const cpx<double> ww = w[id];
-    out[id] = cpx<T>{T(u.re), T(u.im)};
-    out[g.NZL + id] = cpx<T>{T(v.re), T(v.im)};
-    out[2 * g.NZL + id] = cpx<T>{T(ww.re), T(ww.im)};
-    if (!g.sp) {
-      const cpx<double> p = phi[id];
-      if (six) {   // dx phi is formed by the x stage
-        const cpx<double> f[3] = {p, ti(ky, p), dphi[id]};
-#pragma unroll
-        for (int k = 0; k < 3; ++k) out[(k + 3) * g.NZL + id] = cpx<T>{T(f[k].re), T(f[k].im)};
-      } else {
-        const cpx<double> f[4] = {p, ti(kx, p), ti(ky, p), dphi[id]};
-#pragma unroll
-        for (int k = 0; k < 4; ++k) out[(k + 3) * g.NZL + id] = cpx<T>{T(f[k].re), T(f[k].im)};
-      }
-    }
-  }
-}
-
-template <typename T>
-__global__ void k_ch_products(ChanGeom g, T* __restrict__ f, T cs) {
-  if (g.sp) {
-    PSMS_GRID_LOOP(id, g.P) {
-      const T u = f[id], v = f[g.P + id], w = f[2 * g.P + id];
-      f[id] = -u * u;
-      f[g.P + id] = -v * v;
-      f[2 * g.P + id] = -w * w;
-      f[3 * g.P + id] = -u * v;
-      f[4 * g.P + id] = -u * w;
-      f[5 * g.P + id] = -v * w;
-    }
-    return;
-  }
-  PSMS_GRID_LOOP(id, g.P) {
-    const T u = f[id], v = f[g.P + id], w = f[2 * g.P + id], p = f[3 * g.P + id];
-    const T gx = f[4 * g.P + id], gy = f[5 * g.P + id], gz = f[6 * g.P + id];
-    f[id] = -u * u + cs * (gy * gy + gz * gz);          // T_xx
-    f[g.P + id] = -v * v + cs * (gx * gx + gz * gz);    // T_yy
-    f[2 * g.P + id] = -w * w + cs * (gx * gx + gy * gy);  // T_zz
-    f[3 * g.P + id] = -u * v - cs * gx * gy;            // T_xy
-    f[4 * g.P + id] = -u * w - cs * gx * gz;            // T_xz
-    f[5 * g.P + id] = -v * w - cs * gy * gz;            // T_yz
-    f[6 * g.P + id] = u * gx + v * gy + w * gz;         // u . grad phi
-    f[7 * g.P + id] = p * p * p;                        // phi^3
+    out[id] = u;
+    out[g.NZL + id] = v;
+    out[2 * g.NZL + id] = w[id];
   }
 }
 
@@ -347,16 +303,10 @@ hipError_t launch_ch_diag_final(const ChanGeom& g, const double* part, int nb1, 
   return hipGetLastError();
 }
 
-template <typename T>
-hipError_t launch_ch_fields(const ChanGeom& g, const cpx<double>* om, const cpx<double>* w, const cpx<double>* phi,
-                            const cpx<double>* dw, const cpx<double>* dphi, const cpx<double>* mean, const double* kx,
-                            const double* ky, cpx<T>* out, hipStream_t st, int six) {
-  k_ch_fields<T><<<blocks_for(g.NZL), kThreads, 0, st>>>(g, om, w, phi, dw, dphi, mean, kx, ky, out, six);
-  return hipGetLastError();
-}
-template <typename T>
-hipError_t launch_ch_products(const ChanGeom& g, T* f, double csig, hipStream_t st) {
-  k_ch_products<T><<<blocks_for(g.P), kThreads, 0, st>>>(g, f, T(csig));
+hipError_t launch_ch_uvw(const ChanGeom& g, const cpx<double>* om, const cpx<double>* w, const cpx<double>* dw,
+                         const cpx<double>* mean, const double* kx, const double* ky, cpx<double>* out,
+                         hipStream_t st) {
+  k_ch_uvw<<<blocks_for(g.NZL), kThreads, 0, st>>>(g, om, w, dw, mean, kx, ky, out);
   return hipGetLastError();
 }
 hipError_t launch_ch_init(const ChanGeom& g, const cpx<double>* U4, const double* kx, const double* ky,
@@ -368,16 +318,5 @@ hipError_t launch_ch_mean_io(const ChanGeom& g, const cpx<double>* in, cpx<doubl
   k_ch_mean_io<<<blocks_for(2LL * (g.nc + 1)), kThreads, 0, st>>>(g.nc + 1, in, out, dir);
   return hipGetLastError();
 }
-
-template hipError_t launch_ch_fields<float>(const ChanGeom&, const cpx<double>*, const cpx<double>*,
-                                            const cpx<double>*, const cpx<double>*, const cpx<double>*,
-                                            const cpx<double>*, const double*, const double*, cpx<float>*,
-                                            hipStream_t, int);
-template hipError_t launch_ch_fields<double>(const ChanGeom&, const cpx<double>*, const cpx<double>*,
-                                             const cpx<double>*, const cpx<double>*, const cpx<double>*,
-                                             const cpx<double>*, const double*, const double*, cpx<double>*,
-                                             hipStream_t, int);
-template hipError_t launch_ch_products<float>(const ChanGeom&, float*, double, hipStream_t);
-template hipError_t launch_ch_products<double>(const ChanGeom&, double*, double, hipStream_t);
 
 }  // namespace psms

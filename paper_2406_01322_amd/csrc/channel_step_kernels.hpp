@@ -18,7 +18,6 @@ struct ChanGeom {
   long long NZL;           // (nc + 1) * NL
   long long P;             // (nc + 1) * ny * nx physical points
   int sp;                  // single phase: phi = 0, no Korteweg stress, no CH terms
-  int nf_in, nf_out;       // fields transformed to physical space / back (7, 8; 3, 6 single phase)
 };
 
 struct ChanCoef {
@@ -27,17 +26,10 @@ struct ChanCoef {
   double csig;
 };
 
-// the 7 spectral fields u, v, w, phi, i kx phi, i ky phi, D phi (precision T);
-// with six, the 6 fields u, v, w, phi, i ky phi, D phi (the fused x stage
-// forms i kx phi itself); u, v, w only in single phase
-template <typename T>
-hipError_t launch_ch_fields(const ChanGeom& g, const cpx<double>* om, const cpx<double>* w, const cpx<double>* phi,
-                            const cpx<double>* dw, const cpx<double>* dphi, const cpx<double>* mean, const double* kx,
-                            const double* ky, cpx<T>* out, hipStream_t st, int six = 0);
-// pointwise products, 7 physical fields in, 8 out (in place, [8][P]); single
-// phase 3 in, the 6 components of -u_i u_j out
-template <typename T>
-hipError_t launch_ch_products(const ChanGeom& g, T* f, double csig, hipStream_t st);
+// u, v, w of a state, [3][NZL]
+hipError_t launch_ch_uvw(const ChanGeom& g, const cpx<double>* om, const cpx<double>* w, const cpx<double>* dw,
+                         const cpx<double>* mean, const double* kx, const double* ky, cpx<double>* out,
+                         hipStream_t st);
 // initial state from the 4 transformed physical fields u, v, w, phi ([4][NZL], FP64;
 // 3 in single phase, phi set to zero)
 hipError_t launch_ch_init(const ChanGeom& g, const cpx<double>* U4, const double* kx, const double* ky,

@@ -123,6 +123,29 @@ def test_channel_step_sizes_and_walls(nx, ny, nc, walls, single):
             assert np.max(np.abs(a - b)) <= 1e-12 * max(np.max(np.abs(b)), 1e-300)
 
 
+# The single-phase x stage (3 fields in, 6 products out) over line lengths with one
+# and with several workgroups, partly filled ones among them, in both field groupings:
+# an AB1 and an AB2 step against the oracle, FP64 to 1e-12 and MIXED to 1e-5 of each
+# field's maximum, as for the other single-phase step tests.
+@pytest.mark.parametrize("nx,ny", [(8, 12), (12, 8), (48, 8), (96, 12), (128, 8), (192, 8), (256, 8)])
+@pytest.mark.parametrize("precision,tol", [("fp64", 1e-12), ("mixed", 1e-5)])
+def test_single_phase_x_stage(nx, ny, precision, tol):
+    from oracle import channel_step as cs
+    from paper_2406_01322_amd.psms import Channel
+    prm = cs.ChannelParams(nx=nx, ny=ny, nc=8, re=20.0, we=1.0, ch=0.2, pe=5.0, dt=1e-3)
+    f = list(_channel_fields(nx, ny, 8, 7))
+    f[3] = np.zeros_like(f[3])
+    c = Channel(nx, ny, 8, prm.re, prm.we, prm.ch, prm.pe, prm.dt, precision=precision, single_phase=True)
+    c.init_state(*[_dev(x) for x in f])
+    st = cs.init_state(*f, prm)
+    for _ in range(2):
+        c.step(1)
+        st = cs.step(st, prm)
+        got, mean = (_host(x) for x in c.get_state())
+        for a, b in ((got[0], st["om"]), (got[1], st["w"]), (mean, st["mean"])):
+            assert np.max(np.abs(a - b)) <= tol * max(np.max(np.abs(b)), 1e-300)
+
+
 # The boundary rows of the solutions for the longer chains (17 slots a piece at nc =
 # 256), to the bars that the wall-solve tests hold them to: 1e-12 of the field's
 # maximum for a value at a wall, 1e-9 for a slope (weights n^2).

@@ -43,6 +43,188 @@ struct CTile {
 
 }  // namespace
 
+// Where the DCT kernels read their input: an array [field][n][line] (ArraySrc), the
+// channel step's fields formed from the FP64 state as they are loaded
+// (ChanFieldSrc: u, v by continuity and the definition of omega_z, w, phi, i ky phi,
+// D phi), or its combinations of the products (ChanTermSrc).  The last two serve
+// two transforms that share inputs to one workgroup: pair Q reads Raw values at a
+// point (all rows of a thread are loaded before the first is used) and forms both
+// inputs from them.  field(q, side): the transform of a pair's side.
+template <typename T>
+struct ArraySrc {
+  static constexpr int kPairs = 1, kSides = 1;
+  const cpx<T>* in;
+  long long fstride;
+  struct Line {};
+  using Raw = cpx<T>;
+  __device__ __forceinline__ Line at(long long) const { return {}; }
+  __device__ __forceinline__ static int field(int q, int) { return q; }
+  template <int Q>
+  __device__ __forceinline__ Raw load(long long id) const {
+    return in[(long long)blockIdx.y * fstride + id];
+  }
+  template <int Q>
+  __device__ __forceinline__ void form(const Raw& r, const Line&, bool, int, long long, cpx<T>& a, cpx<T>&) const {
+    a = r;
+  }
+};
+template <typename T>
+struct ChanFieldSrcT {
+  static constexpr int kPairs = 3, kSides = 2;
+  ChanFieldSrc s;
+  struct Line {
+    double kx, ky, ik2;
+  };
+  struct Raw {
+    cpx<double> x[2];
+  };
+  __device__ __forceinline__ Line at(long long l) const {
+    const double kx = s.kx[l], ky = s.ky[l];
+    return Line{kx, ky, 1.0 / (kx * kx + ky * ky)};
+  }
+  // (u, v), (w, D phi), (phi, i ky phi)
+  __device__ __forceinline__ static int field(int q, int side) {
+    return q == 0 ? side : q == 1 ? 2 + 3 * side : 3 + side;
+  }
+  template <int Q>
+  __device__ __forceinline__ Raw load(long long id) const {
+    if constexpr (Q == 0) return Raw{{s.om[id], s.dw[id]}};
+    else if constexpr (Q == 1) return Raw{{s.w[id], s.dphi[id]}};
+    else return Raw{{s.phi[id], cpx<double>{0.0, 0.0}}};
+  }
+  template <int Q>
+  __device__ __forceinline__ void form(const Raw& r, const Line& k, bool mean, int j, long long id, cpx<T>& a,
+                                       cpx<T>& b) const {
+    cpx<double> x, y;
+    if constexpr (Q == 0) {
+      const cpx<double> o = r.x[0], d = r.x[1];
+      const cpx<double> p = {k.kx * d.re + k.ky * o.re, k.kx * d.im + k.ky * o.im};
+      const cpx<double> q = {k.ky * d.re - k.kx * o.re, k.ky * d.im - k.kx * o.im};
+      x = cpx<double>{k.ik2 * (-1.0 * p.im), k.ik2 * (1.0 * p.re)};   // i p / k^2
+      y = cpx<double>{k.ik2 * (-1.0 * q.im), k.ik2 * (1.0 * q.re)};
+      if (mean) {                                                     // the mean line carries U, V
+        x = s.mean[2 * j];
+        y = s.mean[2 * j + 1];
+      }
+    } else if constexpr (Q == 1) {
+      x = r.x[0];
+      y = r.x[1];
+    } else {
+      x = r.x[0];
+      y = cpx<double>{-k.ky * x.im, k.ky * x.re};
+    }
+    a = cpx<T>{T(x.re), T(x.im)};
+    b = cpx<T>{T(y.re), T(y.im)};
+  }
+};
+
+// The combinations of the transformed products that the wall-normal right-hand
+// sides need, formed in FP64 from the y-forward output [8][j][line] and rounded
+// once to the transform's precision: four transforms and FP64 arrays in place of
+// six.
+template <typename T>
+struct ChanTermSrcT {
+  static constexpr int kPairs = 3, kSides = 2;
+  const cpx<T>* t;   // T_xx T_yy T_zz T_xy T_xz T_yz (a, c), fstride apart
+  long long fstride;
+  const double* kxl;
+  const double* kyl;
+  struct Line {
+    double kx, ky;
+  };
+  struct Raw {
+    cpx<T> x[4];
+  };
+  __device__ __forceinline__ Line at(long long l) const { return Line{kxl[l], kyl[l]}; }
+  // (A, Q), (B, P), (a, c)
+  __device__ __forceinline__ static int field(int q, int side) {
+    return q == 0 ? 3 * side : q == 1 ? 1 + side : 4 + side;
+  }
+  template <int Q>
+  __device__ __forceinline__ Raw load(long long id) const {
+    const cpx<T> z = {T(0), T(0)};
+    if constexpr (Q == 0) return Raw{{t[id], t[fstride + id], t[2 * fstride + id], t[3 * fstride + id]}};
+    else return Raw{{t[(2 + 2 * Q) * fstride + id], t[(3 + 2 * Q) * fstride + id], z, z}};
+  }
+  template <int Q>
+  __device__ __forceinline__ void form(const Raw& r, const Line& k, bool mean, int j, long long id, cpx<T>& a,
+                                       cpx<T>& b) const {
+    if constexpr (Q == 2) {
+      a = r.x[0];
+      b = r.x[1];
+      return;
+    }
+    auto up = [](cpx<T> v) { return cpx<double>{double(v.re), double(v.im)}; };
+    const double kx = k.kx, ky = k.ky;
+    cpx<double> x, y;
+    if constexpr (Q == 0) {
+      // (ky^2 - kx^2) T_xy + kx ky (T_xx - T_yy); kx^2 T_xx + 2 kx ky T_xy + ky^2 T_yy - k^2 T_zz
+      const cpx<double> xx = up(r.x[0]), yy = up(r.x[1]), zz = up(r.x[2]), xy = up(r.x[3]);
+      const double ca = ky * ky - kx * kx, cb = kx * ky;
+      x = cpx<double>{ca * xy.re + cb * (xx.re - yy.re), ca * xy.im + cb * (xx.im - yy.im)};
+      const double da = kx * kx, db = 2.0 * kx * ky, dc = ky * ky, dd = da + dc;
+      y = cpx<double>{da * xx.re + db * xy.re + dc * yy.re - dd * zz.re, da * xx.im + db * xy.im + dc * yy.im - dd * zz.im};
+    } else {
+      // i kx T_yz - i ky T_xz, i kx T_xz + i ky T_yz
+      const cpx<double> xz = up(r.x[0]), yz = up(r.x[1]);
+      x = cpx<double>{-(kx * yz.im - ky * xz.im), kx * yz.re - ky * xz.re};
+      y = cpx<double>{-(kx * xz.im + ky * yz.im), kx * xz.re + ky * yz.re};
+    }
+    a = cpx<T>{T(x.re), T(x.im)};
+    b = cpx<T>{T(y.re), T(y.im)};
+    if (mean) {   // the mean line: T_xz in the second array, T_yz in the fourth
+      a = Q == 0 ? cpx<T>{T(0), T(0)} : r.x[0];
+      b = Q == 0 ? t[5 * fstride + id] : cpx<T>{T(0), T(0)};
+    }
+  }
+};
+
+// f(integral_constant<int, q>) for the run-time pair q (uniform in a workgroup)
+template <class Src, class F>
+__device__ __forceinline__ void with_pair(int q, F&& f) {
+  if constexpr (Src::kPairs == 1) f(std::integral_constant<int, 0>{});
+  else if (q == 0) f(std::integral_constant<int, 0>{});
+  else if (q == 1) f(std::integral_constant<int, 1>{});
+  else f(std::integral_constant<int, 2>{});
+}
+
+// The workgroup's lines staged through LDS: each input is read once (a transform's
+// positions need x_j twice), and a pair's inputs for both its sides.  The step's
+// transforms are bound by these reads and their writes: at 256 x 256 x 257 in FP64
+// the products' took 350 us and the fields' 211 with a workgroup a field reading
+// each input twice, 206 and 150 so (0.52 and 0.24 GB); at 256 x 128 x 129 in FP32
+// 54 and 48 us, now 34 and 33.
+// put(j, a, b) with the sides' inputs a[0], b[0] at j = 0 .. NC, a thread's rows
+// being t, t + TT, ..; PAIRED: j = 0 .. NC / 2, and a[1], b[1] at NC - j.
+template <typename T, class Src, int NC, int TT, bool PAIRED, class Put>
+__device__ __forceinline__ void dct_stage(const Src& src, int q, int t, long long l, long long nlines, bool mean,
+                                          Put&& put) {
+  constexpr int NJ = PAIRED ? NC / 2 : NC;         // rows 0 .. NJ
+  constexpr int NR = NJ / TT;                      // whole rounds; then the rows past them
+  static_assert(NR * TT <= NJ && (NR + 1) * TT > NJ, "rows");
+  const typename Src::Line k = src.at(l);
+  with_pair<Src>(q, [&](auto qi) {
+    constexpr int Q = decltype(qi)::value;
+    typename Src::Raw ra[NR + 1], rb[PAIRED ? NR + 1 : 1];
+    const bool more = t <= NJ - NR * TT;
+#pragma unroll
+    for (int i = 0; i <= NR; ++i) {
+      const int j = t + ((i < NR || more) ? i * TT : 0);
+      ra[i] = src.template load<Q>((long long)j * nlines + l);
+      if constexpr (PAIRED) rb[i] = src.template load<Q>((long long)(NC - j) * nlines + l);
+    }
+#pragma unroll
+    for (int i = 0; i <= NR; ++i) {
+      if (i == NR && !more) break;
+      const int j = t + i * TT;
+      cpx<T> a[2] = {}, b[2] = {};   // at j and NC - j
+      src.template form<Q>(ra[i], k, mean, j, (long long)j * nlines + l, a[0], b[0]);
+      if constexpr (PAIRED) src.template form<Q>(rb[i], k, mean, NC - j, (long long)(NC - j) * nlines + l, a[1], b[1]);
+      put(j, a, b);
+    }
+  });
+}
+
 // dir = +1: values at the CGL points -> Chebyshev coefficients,
 //   a_n = G_n / (nc cbar_n),  G = FFT of the even extension of f;
 // dir = -1: coefficients -> values, f_j = FFT of the even extension of b with
@@ -50,105 +232,23 @@ struct CTile {
 // out64 (forward only, if not NULL): the coefficients n <= kz are written in
 // FP64 instead (the products' Chebyshev truncation; its reader takes the others
 // as zero), so the step needs no separate promotion pass.
-// Where the DCT kernels read their input value of field f, coefficient j, line
-// l: an array [field][n][line] (ArraySrc), or the channel step's fields formed
-// from the FP64 state as they are loaded (ChanFieldSrc: u, v by continuity and
-// the definition of omega_z, w, phi, i ky phi, D phi).
-template <typename T>
-struct ArraySrc {
-  const cpx<T>* in;
-  long long fstride, nlines;
-  __device__ __forceinline__ cpx<T> operator()(int f, long long j, long long l) const {
-    return in[f * fstride + j * nlines + l];
-  }
-};
-template <typename T>
-struct ChanFieldSrcT {
-  ChanFieldSrc s;
-  __device__ __forceinline__ cpx<T> operator()(int f, long long j, long long l) const {
-    const long long id = j * s.nlines + l;
-    cpx<double> x;
-    if (f <= 1) {
-      if (l == 0) {                          // the mean line carries U, V
-        x = s.mean[2 * j + f];
-      } else {
-        const double kx = s.kx[l], ky = s.ky[l];
-        const double ik2 = 1.0 / (kx * kx + ky * ky);
-        const cpx<double> o = s.om[id], d = s.dw[id];
-        const cpx<double> a = (f == 0) ? cpx<double>{kx * d.re + ky * o.re, kx * d.im + ky * o.im}
-                                       : cpx<double>{ky * d.re - kx * o.re, ky * d.im - kx * o.im};
-        x = cpx<double>{ik2 * (-1.0 * a.im), ik2 * (1.0 * a.re)};   // i a / k^2
-      }
-    } else if (f == 2) {
-      x = s.w[id];
-    } else if (f == 3) {
-      x = s.phi[id];
-    } else if (f == 4) {
-      const double ky = s.ky[l];
-      const cpx<double> p = s.phi[id];
-      x = cpx<double>{-ky * p.im, ky * p.re};
-    } else {
-      x = s.dphi[id];
-    }
-    return cpx<T>{T(x.re), T(x.im)};
-  }
-};
-
-// The combinations of the transformed products that the wall-normal right-hand
-// sides need (ChanTermSrc), formed in FP64 from the y-forward output
-// [8][j][line] and rounded once to the transform's precision: four transforms
-// and FP64 arrays in place of six.
-template <typename T>
-struct ChanTermSrcT {
-  const cpx<T>* t;   // T_xx T_yy T_zz T_xy T_xz T_yz (a, c), fstride apart
-  long long fstride, nlines;
-  const double* kxl;
-  const double* kyl;
-  __device__ __forceinline__ cpx<double> get(int f, long long id) const {
-    const cpx<T> v = t[f * fstride + id];
-    return cpx<double>{double(v.re), double(v.im)};
-  }
-  __device__ __forceinline__ cpx<T> operator()(int f, long long j, long long l) const {
-    const long long id = j * nlines + l;
-    if (f >= 4) return t[(f + 2) * fstride + id];
-    if (l == 0) {   // the mean line: T_xz and T_yz in the second and fourth array
-      const cpx<T> m = t[(f == 1 ? 4 : 5) * fstride + id];
-      return (f & 1) ? m : cpx<T>{T(0), T(0)};
-    }
-    const double kx = kxl[l], ky = kyl[l];
-    cpx<double> x;
-    if (f == 0) {          // (ky^2 - kx^2) T_xy + kx ky (T_xx - T_yy)
-      const cpx<double> xx = get(0, id), yy = get(1, id), xy = get(3, id);
-      const double a = ky * ky - kx * kx, b = kx * ky;
-      x = cpx<double>{a * xy.re + b * (xx.re - yy.re), a * xy.im + b * (xx.im - yy.im)};
-    } else if (f == 3) {   // kx^2 T_xx + 2 kx ky T_xy + ky^2 T_yy - k^2 T_zz
-      const cpx<double> xx = get(0, id), yy = get(1, id), zz = get(2, id), xy = get(3, id);
-      const double a = kx * kx, b = 2.0 * kx * ky, c = ky * ky, d = a + c;
-      x = cpx<double>{a * xx.re + b * xy.re + c * yy.re - d * zz.re, a * xx.im + b * xy.im + c * yy.im - d * zz.im};
-    } else {               // i kx T_yz - i ky T_xz, i kx T_xz + i ky T_yz
-      const cpx<double> xz = get(4, id), yz = get(5, id);
-      const double a = f == 1 ? -ky : kx, b = f == 1 ? kx : ky;   // of T_xz, T_yz
-      x = cpx<double>{-(a * xz.im + b * yz.im), a * xz.re + b * yz.re};
-    }
-    return cpx<T>{T(x.re), T(x.im)};
-  }
-};
-
+// both: a workgroup transforms both sides of a pair, one after the other; else
+// each side has a workgroup (blockIdx.y = 2 pair + side).
 template <typename T, int N, class Src>
-__global__ void __launch_bounds__(1024) k_dct(Src src, cpx<T>* __restrict__ out,
-                                             long long nlines, int dir, long long fstride,
-                                             const cpx<T>* __restrict__ tw_g, cpx<double>* __restrict__ out64,
-                                             int kz) {
+__global__ void __launch_bounds__(CTile<Plan<N>>::L * CTile<Plan<N>>::TT) k_dct(Src src, cpx<T>* __restrict__ out, long long nlines, int nfield,
+                                             int both, int dir, long long fstride, const cpx<T>* __restrict__ tw_g,
+                                             cpx<double>* __restrict__ out64, int kz) {
   using P = Plan<N>;
   using G = CTile<P>;
-  constexpr int E = G::E, L = G::L, LP = L + 1, NC = N / 2;
+  constexpr int E = G::E, L = G::L, LP = L + 1, TT = G::TT, NC = N / 2;
   constexpr int RI = first_radix<P, -1>(), RO = last_radix<P, -1>();
   __shared__ cpx<T> tw[N];
   __shared__ cpx<T> lds[2][N * LP];
   const int tid = threadIdx.x;
   const int line = tid % L, t = tid / L;
-  if (out) out += (long long)blockIdx.y * fstride;   // field blockIdx.y
-  if (out64) out64 += (long long)blockIdx.y * fstride;
+  const int q = (Src::kSides == 1 || both) ? blockIdx.y : blockIdx.y / 2;
+  const int side0 = (Src::kSides == 1 || both) ? 0 : blockIdx.y % 2, side1 = (Src::kSides == 2 && both) ? 1 : side0;
+  if (src.field(q, side0) >= nfield) return;
   if (tw_g) {
     for (int i = tid; i < N; i += blockDim.x) tw[i] = tw_g[i];
   } else {
@@ -158,47 +258,58 @@ __global__ void __launch_bounds__(1024) k_dct(Src src, cpx<T>* __restrict__ out,
       tw[i] = cpx<T>{T(c), T(s)};
     }
   }
-  const long long l = (long long)blockIdx.x * L + line;
+  const long long l = (long long)xcd_tile(blockIdx.x, gridDim.x) * L + line;
   const bool valid = l < nlines;
-  cpx<T> v[E];
-#pragma unroll
-  for (int b = 0; b < E / RI; ++b)
-#pragma unroll
-    for (int r = 0; r < RI; ++r) {
-      const int p = slot_pos<P, RI>(t, b, r);
-      const int j = (p <= NC) ? p : N - p;
-      cpx<T> x = {T(0), T(0)};
-      if (valid) {
-        x = src(int(blockIdx.y), j, l);
-        if (dir < 0 && j != 0 && j != NC) {
-          x.re *= T(0.5);
-          x.im *= T(0.5);
-        }
-      }
-      v[b * RI + r] = x;
+  const IdxPosMajor idx{LP, line};
+  dct_stage<T, Src, NC, TT, false>(src, q, t, valid ? l : nlines - 1, nlines, l == 0, [&](int j, cpx<T>* a, cpx<T>* b) {
+    if (dir < 0 && j != 0 && j != NC) {
+      a[0] = cpx<T>{T(0.5) * a[0].re, T(0.5) * a[0].im};
+      b[0] = cpx<T>{T(0.5) * b[0].re, T(0.5) * b[0].im};
     }
+    if (side0 == 0) lds[0][idx(j)] = a[0];
+    if (Src::kSides == 2 && side1 == 1) lds[1][idx(j)] = b[0];
+  });
   __syncthreads();
-  int par = 0;
-  fft_line<T, P, -1>(v, lds[0], lds[1], par, t, IdxPosMajor{LP, line}, tw);
-  if (valid) {
+  // the even extension at the positions the FFT starts from
+  cpx<T> v[Src::kSides][E];
 #pragma unroll
-    for (int b = 0; b < E / RO; ++b)
+  for (int h = 0; h < Src::kSides; ++h)
+    if (h >= side0 && h <= side1) {
 #pragma unroll
-      for (int r = 0; r < RO; ++r) {
-        const int p = slot_pos<P, RO>(t, b, r);
-        if (p <= NC) {
-          cpx<T> x = v[b * RO + r];
-          if (dir > 0) {
-            const T sc = T(1.0 / (double(NC) * ((p == 0 || p == NC) ? 2.0 : 1.0)));
-            x.re *= sc;
-            x.im *= sc;
-          }
-          if (!out64)
-            out[(long long)p * nlines + l] = x;
-          else if (p <= kz)
-            out64[(long long)p * nlines + l] = cpx<double>{double(x.re), double(x.im)};
+      for (int b = 0; b < E / RI; ++b)
+#pragma unroll
+        for (int r = 0; r < RI; ++r) {
+          const int p = slot_pos<P, RI>(t, b, r);
+          v[h][b * RI + r] = lds[h][idx((p <= NC) ? p : N - p)];
         }
-      }
+    }
+#pragma unroll
+  for (int h = 0; h < Src::kSides; ++h) {
+    if (h < side0 || h > side1 || src.field(q, h) >= nfield) continue;
+    __syncthreads();   // the staged lines (the previous transform's exchanges) have been read
+    int par = 0;
+    fft_line<T, P, -1>(v[h], lds[0], lds[1], par, t, idx, tw);
+    if (valid) {
+      const long long fo = (long long)src.field(q, h) * fstride;
+#pragma unroll
+      for (int b = 0; b < E / RO; ++b)
+#pragma unroll
+        for (int r = 0; r < RO; ++r) {
+          const int p = slot_pos<P, RO>(t, b, r);
+          if (p <= NC) {
+            cpx<T> x = v[h][b * RO + r];
+            if (dir > 0) {
+              const T sc = T(1.0 / (double(NC) * ((p == 0 || p == NC) ? 2.0 : 1.0)));
+              x.re *= sc;
+              x.im *= sc;
+            }
+            if (!out64)
+              out[fo + (long long)p * nlines + l] = x;
+            else if (p <= kz)
+              out64[fo + (long long)p * nlines + l] = cpx<double>{double(x.re), double(x.im)};
+          }
+        }
+    }
   }
 }
 
@@ -217,8 +328,8 @@ __global__ void __launch_bounds__(1024) k_dct(Src src, cpx<T>* __restrict__ out,
 // starting value.  dir = +1: x = f, a_n = 2 C_n / (nc cbar_n); dir = -1:
 // x = cbar a, f_j = C_j.  tw_g: exp(-i pi m / nc), m < 2 nc (or NULL).
 template <typename T, int NC, class Src>
-__global__ void __launch_bounds__(1024) k_dct_half(Src src, cpx<T>* __restrict__ out,
-                                                  long long nlines, int dir, long long fstride,
+__global__ void __launch_bounds__(CTile<Plan<NC>>::L * CTile<Plan<NC>>::TT) k_dct_half(Src src, cpx<T>* __restrict__ out, long long nlines, int nfield,
+                                                  int both, int dir, long long fstride,
                                                   const cpx<T>* __restrict__ tw_g, cpx<double>* __restrict__ out64,
                                                   int kz) {
   using P = Plan<NC>;
@@ -228,14 +339,17 @@ __global__ void __launch_bounds__(1024) k_dct_half(Src src, cpx<T>* __restrict__
   constexpr int NK = NC / 2 - 1;                 // increments of the odd orders, k = 1 .. NC/2 - 1
   constexpr int CS = (NK + TT - 1) / TT;         // a thread's run of k
   static_assert(2 * NC * LP * int(sizeof(cpx<T>)) + 3 * NC * int(sizeof(cpx<T>)) <= 160 * 1024, "LDS");
-  static_assert(TT * L * 2 * 16 <= NC * LP * int(sizeof(cpx<T>)), "partial sums fit one exchange buffer");
+  constexpr int TW = (64 / L < TT) ? 64 / L : TT, NW = TT / TW;   // threads of a line in a wavefront, wavefronts
+  static_assert(64 % L == 0 && TT % TW == 0, "lane = line + L (t mod TW)");
+  static_assert(NW * L * 2 * 16 <= NC * LP * int(sizeof(cpx<T>)), "partial sums fit one exchange buffer");
   __shared__ cpx<T> tw2[2 * NC];                 // exp(-i pi m / NC)
   __shared__ cpx<T> tw[NC];                      // exp(-2 pi i m / NC)
   __shared__ cpx<T> lds[2][NC * LP];
   const int tid = threadIdx.x;
   const int line = tid % L, t = tid / L;
-  if (out) out += (long long)blockIdx.y * fstride;
-  if (out64) out64 += (long long)blockIdx.y * fstride;
+  const int q = (Src::kSides == 1 || both) ? blockIdx.y : blockIdx.y / 2;
+  const int side0 = (Src::kSides == 1 || both) ? 0 : blockIdx.y % 2, side1 = (Src::kSides == 2 && both) ? 1 : side0;
+  if (src.field(q, side0) >= nfield) return;
   for (int i = tid; i < 2 * NC; i += blockDim.x) {
     cpx<T> w;
     if (tw_g) {
@@ -248,103 +362,122 @@ __global__ void __launch_bounds__(1024) k_dct_half(Src src, cpx<T>* __restrict__
     tw2[i] = w;
     if (!(i & 1)) tw[i >> 1] = w;
   }
-  const long long l = (long long)blockIdx.x * L + line;
+  const long long l = (long long)xcd_tile(blockIdx.x, gridDim.x) * L + line;
   const bool valid = l < nlines;
+  const IdxPosMajor idx{LP, line};
   __syncthreads();
-  // y at the positions the FFT starts from, and this thread's share of C_1
-  cpx<T> v[E];
-  double c1r = 0.0, c1i = 0.0;
+  // y of each side, and this thread's share of its C_1
+  double c1r[Src::kSides] = {}, c1i[Src::kSides] = {};
+  dct_stage<T, Src, NC, TT, true>(src, q, t, valid ? l : nlines - 1, nlines, l == 0, [&](int j, cpx<T>* a, cpx<T>* b) {
+    const T cj = tw2[j].re, sj = -tw2[j].im;   // cos, sin (pi j / NC)
 #pragma unroll
-  for (int b = 0; b < E / RI; ++b)
-#pragma unroll
-    for (int r = 0; r < RI; ++r) {
-      const int j = slot_pos<P, RI>(t, b, r);    // 0 .. NC-1
-      cpx<T> y = {T(0), T(0)};
-      if (valid) {
-        cpx<T> xa = src(int(blockIdx.y), j, l);
-        cpx<T> xb = src(int(blockIdx.y), NC - j, l);   // x_{NC-j} (x_NC for j = 0)
-        if (dir < 0 && j == 0) {                 // x = cbar a: the end points doubled
-          xa = cpx<T>{T(2) * xa.re, T(2) * xa.im};
-          xb = cpx<T>{T(2) * xb.re, T(2) * xb.im};
-        }
-        const T cj = tw2[j].re, sj = -tw2[j].im;   // cos, sin (pi j / NC)
-        if (j == 0) {
-          y = cpx<T>{T(0.5) * (xa.re + xb.re), T(0.5) * (xa.im + xb.im)};
-          c1r += 0.5 * double(xa.re) - 0.5 * double(xb.re);   // w_0 x_0 cos 0 + w_NC x_NC cos pi
-          c1i += 0.5 * double(xa.im) - 0.5 * double(xb.im);
-        } else {
-          const cpx<T> sm = {T(0.5) * (xa.re + xb.re), T(0.5) * (xa.im + xb.im)};
-          const cpx<T> df = {xa.re - xb.re, xa.im - xb.im};
-          y = cpx<T>{sm.re - sj * df.re, sm.im - sj * df.im};
-          c1r += double(cj) * double(xa.re);
-          c1i += double(cj) * double(xa.im);
+    for (int h = 0; h < Src::kSides; ++h) {
+      if (h < side0 || h > side1) continue;
+      cpx<T> xa = h ? b[0] : a[0], xb = h ? b[1] : a[1];   // x_j, x_{NC-j}
+      if (dir < 0 && j == 0) {                 // x = cbar a: the end points doubled
+        xa = cpx<T>{T(2) * xa.re, T(2) * xa.im};
+        xb = cpx<T>{T(2) * xb.re, T(2) * xb.im};
+      }
+      const cpx<T> sm = {T(0.5) * (xa.re + xb.re), T(0.5) * (xa.im + xb.im)};
+      const cpx<T> df = {xa.re - xb.re, xa.im - xb.im};
+      if (j == 0) {
+        lds[h][idx(0)] = sm;
+        c1r[h] += 0.5 * double(xa.re) - 0.5 * double(xb.re);   // w_0 x_0 cos 0 + w_NC x_NC cos pi
+        c1i[h] += 0.5 * double(xa.im) - 0.5 * double(xb.im);
+      } else {
+        lds[h][idx(j)] = cpx<T>{sm.re - sj * df.re, sm.im - sj * df.im};
+        if (j != NC / 2) {
+          lds[h][idx(NC - j)] = cpx<T>{sm.re + sj * df.re, sm.im + sj * df.im};
+          c1r[h] += double(cj) * (double(xa.re) - double(xb.re));
+          c1i[h] += double(cj) * (double(xa.im) - double(xb.im));
         }
       }
-      v[b * RI + r] = y;
     }
-  int par = 0;
-  fft_line<T, P, -1>(v, lds[0], lds[1], par, t, IdxPosMajor{LP, line}, tw);
-  // Z in natural order in lds[0]; the partial sums in lds[1] (as doubles)
+  });
   __syncthreads();
-  const IdxPosMajor idx{LP, line};
+  cpx<T> v[Src::kSides][E];
 #pragma unroll
-  for (int b = 0; b < E / RO; ++b)
+  for (int h = 0; h < Src::kSides; ++h)
+    if (h >= side0 && h <= side1) {
 #pragma unroll
-    for (int r = 0; r < RO; ++r) lds[0][idx(slot_pos<P, RO>(t, b, r))] = v[b * RO + r];
-  double* ps = reinterpret_cast<double*>(lds[1]);     // [2][TT][L] pairs (re, im)
-  ps[2 * (t * L + line)] = c1r;
-  ps[2 * (t * L + line) + 1] = c1i;
-  __syncthreads();
-  double s1r = 0.0, s1i = 0.0;                         // C_1 of the line
-#pragma unroll 4
-  for (int u = 0; u < TT; ++u) {
-    s1r += ps[2 * (u * L + line)];
-    s1i += ps[2 * (u * L + line) + 1];
-  }
-  // this thread's run of increments (i/2)(Z_k - Z_{NC-k}), k in [k0, k1)
-  const int k0 = 1 + t * CS, k1 = (k0 + CS <= NK + 1) ? k0 + CS : NK + 1;
-  double rr = 0.0, ri = 0.0;
+      for (int b = 0; b < E / RI; ++b)
+#pragma unroll
+        for (int r = 0; r < RI; ++r) v[h][b * RI + r] = lds[h][idx(slot_pos<P, RI>(t, b, r))];
+    }
+#pragma unroll
+  for (int h = 0; h < Src::kSides; ++h) {
+    if (h < side0 || h > side1 || src.field(q, h) >= nfield) continue;
+    __syncthreads();   // the staged lines (the previous transform's Z and sums) have been read
+    int par = 0;
+    fft_line<T, P, -1>(v[h], lds[0], lds[1], par, t, idx, tw);
+    // Z in natural order in lds[0]
+    __syncthreads();
+#pragma unroll
+    for (int b = 0; b < E / RO; ++b)
+#pragma unroll
+      for (int r = 0; r < RO; ++r) lds[0][idx(slot_pos<P, RO>(t, b, r))] = v[h][b * RO + r];
+    // sums over the TW threads of a line in this wavefront by shuffles, and the
+    // wavefronts' totals through lds[1]
+    cpx<double>* ps = reinterpret_cast<cpx<double>*>(lds[1]);     // [2][TT / TW][L]
+    const int tw_i = t % TW, w = t / TW;
+    cpx<double> c1 = {c1r[h], c1i[h]};
+#pragma unroll
+    for (int d = 1; d < TW; d <<= 1) c1 = cadd(c1, cpx<double>{__shfl_xor(c1.re, L * d), __shfl_xor(c1.im, L * d)});
+    if (tw_i == 0) ps[w * L + line] = c1;
+    __syncthreads();
+    // this thread's run of increments (i/2)(Z_k - Z_{NC-k}), k in [k0, k1)
+    const int k0 = 1 + t * CS, k1 = (k0 + CS <= NK + 1) ? k0 + CS : NK + 1;
+    cpx<double> run = {0.0, 0.0};
 #pragma unroll 2
-  for (int k = k0; k < k1; ++k) {
-    const cpx<T> a = lds[0][idx(k)], c = lds[0][idx(NC - k)];
-    rr += -0.5 * (double(a.im) - double(c.im));
-    ri += 0.5 * (double(a.re) - double(c.re));
-  }
-  ps[2 * TT * L + 2 * (t * L + line)] = rr;
-  ps[2 * TT * L + 2 * (t * L + line) + 1] = ri;
-  __syncthreads();
-  if (!valid) return;
-  auto put = [&](int n, double re, double im) {
-    if (dir > 0) {
-      const double sc = 2.0 / (double(NC) * ((n == 0 || n == NC) ? 2.0 : 1.0));
-      re *= sc;
-      im *= sc;
+    for (int k = k0; k < k1; ++k) {
+      const cpx<T> a = lds[0][idx(k)], c = lds[0][idx(NC - k)];
+      run.re += -0.5 * (double(a.im) - double(c.im));
+      run.im += 0.5 * (double(a.re) - double(c.re));
     }
-    if (!out64)
-      out[(long long)n * nlines + l] = cpx<T>{T(re), T(im)};
-    else if (n <= kz)
-      out64[(long long)n * nlines + l] = cpx<double>{re, im};
-  };
-  // even orders
+    cpx<double> upto = run;   // the runs of this wavefront up to this thread's
+#pragma unroll
+    for (int d = 1; d < TW; d <<= 1) {
+      const cpx<double> o = {__shfl_up(upto.re, L * d), __shfl_up(upto.im, L * d)};
+      if (tw_i >= d) upto = cadd(upto, o);
+    }
+    if (tw_i == TW - 1) ps[(NW + w) * L + line] = upto;
+    cpx<double> before = {__shfl_up(upto.re, L), __shfl_up(upto.im, L)};
+    if (tw_i == 0) before = cpx<double>{0.0, 0.0};
+    __syncthreads();
+    if (!valid) continue;
+    const long long fo = (long long)src.field(q, h) * fstride;
+    auto put = [&](int n, double re, double im) {
+      if (dir > 0) {
+        const double sc = 2.0 / (double(NC) * ((n == 0 || n == NC) ? 2.0 : 1.0));
+        re *= sc;
+        im *= sc;
+      }
+      if (!out64)
+        out[fo + (long long)n * nlines + l] = cpx<T>{T(re), T(im)};
+      else if (n <= kz)
+        out64[fo + (long long)n * nlines + l] = cpx<double>{re, im};
+    };
+    // even orders
 #pragma unroll 1
-  for (int k = t; k <= NC / 2; k += TT) {
-    const cpx<T> a = lds[0][idx(k)], c = lds[0][idx((NC - k) % NC)];
-    put(2 * k, 0.5 * (double(a.re) + double(c.re)), 0.5 * (double(a.im) + double(c.im)));
-  }
-  // odd orders: C_1 plus the runs before this thread's, then its own run
-  double ar = s1r, ai = s1i;
+    for (int k = t; k <= NC / 2; k += TT) {
+      const cpx<T> a = lds[0][idx(k)], c = lds[0][idx((NC - k) % NC)];
+      put(2 * k, 0.5 * (double(a.re) + double(c.re)), 0.5 * (double(a.im) + double(c.im)));
+    }
+    // odd orders: C_1 plus the runs before this thread's, then its own run
+    cpx<double> c = {0.0, 0.0};
 #pragma unroll 4
-  for (int u = 0; u < t; ++u) {
-    ar += ps[2 * TT * L + 2 * (u * L + line)];
-    ai += ps[2 * TT * L + 2 * (u * L + line) + 1];
-  }
-  if (t == 0) put(1, ar, ai);
+    for (int u = 0; u < NW; ++u) c = cadd(c, ps[u * L + line]);
+#pragma unroll 4
+    for (int u = 0; u < w; ++u) c = cadd(c, ps[(NW + u) * L + line]);
+    double ar = c.re + before.re, ai = c.im + before.im;
+    if (t == 0) put(1, ar, ai);
 #pragma unroll 1
-  for (int k = k0; k < k1; ++k) {
-    const cpx<T> a = lds[0][idx(k)], c = lds[0][idx(NC - k)];
-    ar += -0.5 * (double(a.im) - double(c.im));
-    ai += 0.5 * (double(a.re) - double(c.re));
-    put(2 * k + 1, ar, ai);
+    for (int k = k0; k < k1; ++k) {
+      const cpx<T> a = lds[0][idx(k)], c = lds[0][idx(NC - k)];
+      ar += -0.5 * (double(a.im) - double(c.im));
+      ai += 0.5 * (double(a.re) - double(c.re));
+      put(2 * k + 1, ar, ai);
+    }
   }
 }
 
@@ -660,22 +793,36 @@ bool supported_nc(int nc) {
 }
 
 namespace {
+// Both sides of a pair in one workgroup where that still leaves every CU one: it
+// reads the pair's inputs once (two steps of the 256 x 256 x 257 channel: 2593
+// against 2742 us with a workgroup a side; 32 x 24 x 33, ten steps: 550 against 512).
+template <class Src>
+dim3 dct_grid(long long tiles, int nfield, int& both) {
+  const int pairs = Src::kSides == 1 ? nfield : (nfield + 1) / 2;
+  both = Src::kSides == 2 && tiles * pairs >= 256;
+  return dim3(unsigned(tiles), unsigned(Src::kSides == 1 || both ? pairs : 2 * pairs));
+}
 template <typename T, int N, class Src>
 hipError_t dct_n(const Src& in, cpx<T>* out, long long nlines, int dir, long long fstride, int nfield,
                  const cpx<T>* tw, cpx<double>* out64, int kz, hipStream_t st) {
-  // FP64 lines take the nc-point route (measured at nc = 128 on the channel
-  // workload: 56.7 us per launch against 72.1 us for the 2 nc-point FFT); FP32
-  // lines keep the 2 nc-point even extension (40.3 us against 43.4 us: the
-  // FP32 transform is cheaper than the nc-point route's extra loads and
-  // running-sum passes through LDS)
-  if constexpr (N >= 16 && sizeof(T) == 8) {   // nc = N / 2 >= 8
+  // Long FP64 lines take the nc-point route: half the exchange traffic (14706
+  // lines, nc = 96, 128, 256: 15.8, 19.8, 44.5 us against 19.1, 23.1, 49.0).
+  // Short ones keep the even extension, with its three barriers fewer: the steps
+  // of the channels with nc = 32 and 64 take 0.95 and 0.98 of the time.  FP32
+  // lines keep it too: its transform is cheap against the nc-point route's FP64
+  // sums (256 x 128 x 129 step: 1.45 ms against 1.55 for five), and every order
+  // is formed by itself.
+  int both = 0;
+  if constexpr (N >= 192 && sizeof(T) == 8) {   // nc = N / 2 >= 96
     using G = CTile<Plan<N / 2>>;
-    const dim3 grid(unsigned((nlines + G::L - 1) / G::L), unsigned(nfield));
-    k_dct_half<T, N / 2, Src><<<grid, unsigned(G::L * G::TT), 0, st>>>(in, out, nlines, dir, fstride, tw, out64, kz);
+    const dim3 grid = dct_grid<Src>((nlines + G::L - 1) / G::L, nfield, both);
+    k_dct_half<T, N / 2, Src><<<grid, unsigned(G::L * G::TT), 0, st>>>(in, out, nlines, nfield, both, dir, fstride, tw,
+                                                                       out64, kz);
   } else {
     using G = CTile<Plan<N>>;
-    const dim3 grid(unsigned((nlines + G::L - 1) / G::L), unsigned(nfield));
-    k_dct<T, N, Src><<<grid, unsigned(G::L * G::TT), 0, st>>>(in, out, nlines, dir, fstride, tw, out64, kz);
+    const dim3 grid = dct_grid<Src>((nlines + G::L - 1) / G::L, nfield, both);
+    k_dct<T, N, Src><<<grid, unsigned(G::L * G::TT), 0, st>>>(in, out, nlines, nfield, both, dir, fstride, tw, out64,
+                                                              kz);
   }
   return hipGetLastError();
 }
@@ -694,7 +841,7 @@ template <typename T>
 hipError_t launch_dct_fields(int nc, const cpx<T>* in, cpx<T>* out, long long nlines, long long fstride, int nfield,
                              const cpx<T>* tw, int dir, hipStream_t st) {
   if (nfield < 1 || nlines == 0) return hipSuccess;
-  const ArraySrc<T> src{in, fstride, nlines};
+  const ArraySrc<T> src{in, fstride};
   switch (2 * nc) {
 #define PSMS_CASE(NN) case NN: return dct_n<T, NN>(src, out, nlines, dir, fstride, nfield, tw, nullptr, 0, st);
     PSMS_FOR_EACH_2NC(PSMS_CASE)
@@ -707,7 +854,8 @@ template <typename T>
 hipError_t launch_dct_chfields(int nc, const ChanFieldSrc& fs, cpx<T>* out, long long fstride, int nfield,
                                const cpx<T>* tw, hipStream_t st) {
   if (fs.nlines == 0) return hipSuccess;
-  const ChanFieldSrcT<T> src{fs};
+  ChanFieldSrcT<T> src{fs};
+  if (nfield == 3) src.s.dphi = fs.w;   // the pair's other side, not transformed: no reads of its own
   switch (2 * nc) {
 #define PSMS_CASE(NN) case NN: return dct_n<T, NN>(src, out, fs.nlines, -1, fstride, nfield, tw, nullptr, 0, st);
     PSMS_FOR_EACH_2NC(PSMS_CASE)
@@ -724,7 +872,7 @@ template <typename T>
 hipError_t launch_dct_chterms(int nc, const cpx<T>* in, cpx<double>* out, long long nlines, long long fstride, int nterm,
                               const double* kx, const double* ky, const cpx<T>* tw, int kz, hipStream_t st) {
   if (nlines == 0) return hipSuccess;
-  const ChanTermSrcT<T> src{in, fstride, nlines, kx, ky};
+  const ChanTermSrcT<T> src{in, fstride, kx, ky};
   switch (2 * nc) {
 #define PSMS_CASE(NN) case NN: return dct_n<T, NN>(src, (cpx<T>*)nullptr, nlines, +1, fstride, nterm, tw, out, kz, st);
     PSMS_FOR_EACH_2NC(PSMS_CASE)

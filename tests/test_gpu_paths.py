@@ -146,6 +146,27 @@ def test_single_phase_x_stage(nx, ny, precision, tol):
             assert np.max(np.abs(a - b)) <= tol * max(np.max(np.abs(b)), 1e-300)
 
 
+# Grids with enough line tiles for a workgroup to take two of the wall-normal
+# transforms (the smaller ones above give each its own): a step against the oracle,
+# FP64 to 1e-12 and MIXED to 1e-5 of each field's maximum, as for the other step tests.
+@pytest.mark.parametrize("nx,ny,nc,single", [(96, 96, 8, False), (96, 96, 12, True), (96, 64, 48, False)])
+@pytest.mark.parametrize("precision,tol", [("fp64", 1e-12), ("mixed", 1e-5)])
+def test_channel_step_paired_transforms(nx, ny, nc, single, precision, tol):
+    from oracle import channel_step as cs
+    from paper_2406_01322_amd.psms import Channel
+    prm = cs.ChannelParams(nx=nx, ny=ny, nc=nc, re=20.0, we=1.0, ch=0.2, pe=5.0, dt=1e-3)
+    f = list(_channel_fields(nx, ny, nc, 9))
+    if single:
+        f[3] = np.zeros_like(f[3])
+    c = Channel(nx, ny, nc, prm.re, prm.we, prm.ch, prm.pe, prm.dt, precision=precision, single_phase=single)
+    c.init_state(*[_dev(x) for x in f])
+    c.step(1)
+    st = cs.step(cs.init_state(*f, prm), prm)
+    got, mean = (_host(x) for x in c.get_state())
+    for a, b in ((got[0], st["om"]), (got[1], st["w"]), (got[2], st["phi"]), (mean, st["mean"])):
+        assert np.max(np.abs(a - b)) <= tol * max(np.max(np.abs(b)), 1e-300)
+
+
 # The boundary rows of the solutions for the longer chains (17 slots a piece at nc =
 # 256), to the bars that the wall-solve tests hold them to: 1e-12 of the field's
 # maximum for a value at a wall, 1e-9 for a slope (weights n^2).

@@ -3,8 +3,9 @@
 // The step of Sec. 2.2 (steps ii-v) is executed as four kernels per time step,
 // all on the caller's stream:
 //   k_ystep<+1>  y-inverse of u, v, w, phi, d_z phi, plus i k_y phi
-//   k_xstep      x-inverse (7 fields), the pointwise products (Sec. 3.2.2,
+//   k_xfield     x-inverse (7 fields), the pointwise products (Sec. 3.2.2,
 //                Hadamard products) and the x-forward of the 8 products
+//                (k_xstep: FP64 rows of 256)
 //   k_ystep<-1>  y-forward with 2/3 truncation
 //   k_zstep      z-forward, spectral RHS assembly, Leray projection, CN/AB2
 //                (NS) and IE/AB2 (CH) updates, then the z-inverse of the new
@@ -26,7 +27,6 @@
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
-
 
 #include "box_kernels.hpp"
 #include "fft_engine.hpp"
@@ -253,21 +253,6 @@ __global__ void __launch_bounds__(256) k_rows_inv(const cpx<T>* __restrict__ in,
 // the positions the inverse leaves them, which are the positions the forward
 // transform starts from, so the products need no data exchange.
 // ---------------------------------------------------------------------------
-// In FP32 the power-of-two plans up to 128 fit 128 VGPRs without spilling, so
-// the compiler is asked for four waves per SIMD.
-template <typename T, int N>
-constexpr int kXstepWaves = (sizeof(T) == 4 && N <= 128 && (N & (N - 1)) == 0) ? 4 : 1;
-// For those plans the fields are transformed four at a time (one LDS round
-// trip per exchange for four lines; the inverse as fields 0-3, then 4-6) and
-// the exchanges use the XOR-swizzled row layout; measured faster at N = 128
-// (products in fours and the swizzle: 30.5 -> 28.8 us; the inverse in fours
-// as well: a further 0.6 us).
-template <typename T, int N>
-constexpr bool kXstepWide = kXstepWaves<T, N> == 4 && N >= 64;
-// the swizzled layout alone (FP64 at N = 64, 128)
-template <typename T, int N>
-constexpr bool kXstepSwz = kXstepWide<T, N> || (sizeof(T) == 8 && (N == 64 || N == 128));
-
 // Staging of the x stage's inputs through LDS by direct global->LDS copies.
 // A wavefront transforms LPW = 64 / TT consecutive row pairs, i.e. 2 LPW
 // consecutive rows of H retained complex values each: one contiguous run of
@@ -282,11 +267,6 @@ struct XStage {
   static constexpr int PIECES = BYTES / 16;
   static constexpr int NI = (PIECES + 63) / 64;
 };
-// Used where one wavefront holds one line (N = 256): measured faster there,
-// and slower than register loads for the shorter lines.
-template <typename T, int N>
-constexpr bool kXstepDma = (N >= 256);
-
 // Copy the pieces of one field that lie within `left` bytes of src.  dst is
 // the wavefront's staging area (wave-uniform); each active lane's 16 bytes
 // land at dst + 1024 i + 16 lane.
@@ -360,7 +340,7 @@ constexpr int xstep_fwd_order(int f) {
 // 257 in FP64, where x-inverse, products and x-forward as passes of their own,
 // with the physical fields stored between them, took 760 us.
 template <typename T, int N, int V, bool CH = false, bool SP = false>
-__global__ void __launch_bounds__(64 << V) __attribute__((amdgpu_waves_per_eu(kXstepWaves<T, N>)))
+__global__ void __launch_bounds__(64 << V) __attribute__((amdgpu_waves_per_eu(1)))
 k_xstep(const BoxDev* __restrict__ boxes, int box0, const cpx<T>* __restrict__ tw_g, long long xrows, double kxs) {
   using P = Plan<N>;
   using G = Tile<P, V>;
@@ -368,51 +348,30 @@ k_xstep(const BoxDev* __restrict__ boxes, int box0, const cpx<T>* __restrict__ t
   const cpx<T>* __restrict__ yin = static_cast<const cpx<T>*>(bx.bufa);
   cpx<T>* __restrict__ xout = static_cast<cpx<T>*>(bx.bufb);
   const double csig_d = bx.csig;
-  constexpr bool WIDE = kXstepWide<T, N>;
-  constexpr bool SWZ = kXstepSwz<T, N>;
-  constexpr int E = G::E, TT = G::TT, L = G::L, LP = SWZ ? kRowStrideSwz<N> : kRowStride<N>, K = G::K, H = G::H;
+  constexpr int E = G::E, TT = G::TT, L = G::L, LP = kRowStride<N>, K = G::K, H = G::H;
   constexpr int NV = SP ? 3 : 7, NPR = SP ? 6 : 8;   // fields, products
-  constexpr int NFF = !WIDE ? 2 : SP ? 3 : 4;        // products per forward group
+  constexpr int NFF = 2;                             // products per forward group
   constexpr int RI = first_radix<P, 1>();   // inverse starts with R[NST-1]
   constexpr int RP = last_radix<P, 1>();    // inverse ends / forward starts with R[0]
   constexpr int RO = last_radix<P, -1>();   // forward ends with R[NST-1]
   const long long ROWS = CH ? xrows : (long long)N * N;
-  constexpr bool XDMA = kXstepDma<T, N>;
   __shared__ cpx<T> twf[tw_size<P, -1>()];
   __shared__ cpx<T> twi[tw_size<P, 1>()];
   __shared__ cpx<T> lds[NFF][L * LP];
-  __shared__ __attribute__((aligned(16))) char xstage_lds[XDMA ? (64 << V) / 64 * 2 * XStage<T, N, TT, H>::BYTES : 16];
+  __shared__ __attribute__((aligned(16))) char xstage_lds[(64 << V) / 64 * 2 * XStage<T, N, TT, H>::BYTES];
   const int tid = threadIdx.x;
   const int t = tid % TT, line = tid / TT;
   build_twiddles<T, P, -1>(twf, [&](int m) { return tw_g[m]; }, tid, int(blockDim.x));
   build_twiddles<T, P, 1>(twi, [&](int m) { return tw_g[m]; }, tid, int(blockDim.x));
   const long long r0 = ((long long)xcd_tile(blockIdx.x, gridDim.x) * L + line) * 2;
   const bool valid = r0 < ROWS;  // ROWS is even: both rows exist
-  using Idx = std::conditional_t<SWZ, IdxLineSwz<N, TT>, IdxLineMajor<N, TT>>;
-  const Idx idx{line * LP};
+  const IdxLineMajor<N, TT> idx{line * LP};
   int par = 0;
   __syncthreads();
 
   // x-inverse of u v w phi dx_phi dy_phi dz_phi, two fields at a time; each of
-  // the pair exchanges through its own buffer lds[g] (wavefront-local).  Where
-  // registers allow (PF), the loads of the next pair are issued before the
-  // current pair is transformed, so that their latency overlaps the transforms;
-  // under the four-wavefront register budget they would spill.
+  // the pair exchanges through its own buffer lds[g] (wavefront-local)
   cpx<T> ph[NV][E];
-  // raw retained kx of both rows of field vf at slot e (= b RI + r) of the
-  // positions the inverse starts from
-  auto load_raw_slot = [&](int vf, int e, cpx<T>& A, cpx<T>& B) {
-    const int fin = (vf <= 3) ? vf : vf - 1;   // vf 4 is i kx times phi
-    const cpx<T>* src = yin + (long long)fin * ROWS * H;
-    const int p = slot_pos<P, RI>(t, e / RI, e % RI);
-    const int k = (p <= N / 2) ? p : N - p;
-    A = cpx<T>{T(0), T(0)};
-    B = cpx<T>{T(0), T(0)};
-    if (valid && k <= K) {
-      A = ld_global(src + r0 * H + k);
-      B = ld_global(src + (r0 + 1) * H + k);
-    }
-  };
   // the packed complex line z = row0 + i row1 in Hermitian-extended FFT order
   auto pack_slot = [&](int vf, int e, cpx<T> A, cpx<T> B, cpx<T>& z) {
     const int p = slot_pos<P, RI>(t, e / RI, e % RI);
@@ -428,16 +387,7 @@ k_xstep(const BoxDev* __restrict__ boxes, int box0, const cpx<T>* __restrict__ t
     }
     z = (p <= N / 2) ? cpx<T>{A.re - B.im, A.im + B.re} : cpx<T>{A.re + B.im, B.re - A.im};
   };
-  auto load_raw = [&](int vf, cpx<T>* a, cpx<T>* bb) {
-#pragma unroll
-    for (int e = 0; e < E; ++e) load_raw_slot(vf, e, a[e], bb[e]);
-  };
-  auto pack = [&](int vf, const cpx<T>* a, const cpx<T>* bb, cpx<T>* v) {
-#pragma unroll
-    for (int e = 0; e < E; ++e) pack_slot(vf, e, a[e], bb[e], v[e]);
-  };
   constexpr int FS = L * LP;  // buffer of the second transform of a pair
-  constexpr bool PF = kXstepWaves<T, N> == 1;  // registers to spare for prefetching
   // Direct-to-LDS staging: the rows of one field that a wavefront transforms
   // are one contiguous run of XS::BYTES bytes, copied by a few 16-byte
   // global_load_lds instructions into the wavefront's staging area while the
@@ -458,78 +408,30 @@ k_xstep(const BoxDev* __restrict__ boxes, int box0, const cpx<T>* __restrict__ t
       xstage_copy<XS>(src, stg + g * XS::BYTES, lane, left);
     }
   };
-  cpx<T> ra[2][E], rb[2][E];
-  if (XDMA) {
-    dma_pair(0);
-  } else if (PF) {
-    load_raw(0, ra[0], rb[0]);
-    load_raw(1, ra[1], rb[1]);
-  }
-  if constexpr (WIDE) {
-    // four inverse transforms per LDS round trip: fields 0-3, then 4-6
-    static_for<0, SP ? 1 : 2>([&](auto gi) {
-      constexpr int f0 = decltype(gi)::value * 4;
-      constexpr int nf = f0 == 0 && !SP ? 4 : 3;
-      cpx<T> v[nf][E];
-#pragma unroll
-      for (int g = 0; g < nf; ++g)
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-          cpx<T> A, B;
-          load_raw_slot(f0 + g, e, A, B);
-          pack_slot(f0 + g, e, A, B, v[g][e]);
-        }
-      fft_lines<T, P, 1, nf>(v, lds[0], FS, 0, par, t, idx, twi);
-#pragma unroll
-      for (int g = 0; g < nf; ++g)
-#pragma unroll
-        for (int e = 0; e < E; ++e) ph[f0 + g][e] = v[g][e];
-    });
-  } else
+  dma_pair(0);
 #pragma unroll
   for (int vf = 0; vf < NV; vf += 2) {
     const int nf = (vf + 1 < NV) ? 2 : 1;
     cpx<T> v[2][E];
-    if (XDMA) {
-      xstage_wait();
+    xstage_wait();
 #pragma unroll
-      for (int g = 0; g < 2; ++g)
-        if (g < nf) {
-          const cpx<T>* sg = reinterpret_cast<const cpx<T>*>(stg + g * XS::BYTES) + ((tid & 63) / TT) * 2 * H;
+    for (int g = 0; g < 2; ++g)
+      if (g < nf) {
+        const cpx<T>* sg = reinterpret_cast<const cpx<T>*>(stg + g * XS::BYTES) + ((tid & 63) / TT) * 2 * H;
 #pragma unroll
-          for (int e = 0; e < E; ++e) {
-            const int p = slot_pos<P, RI>(t, e / RI, e % RI);
-            const int k = (p <= N / 2) ? p : N - p;
-            cpx<T> A = {T(0), T(0)}, B = {T(0), T(0)};
-            if (valid && k <= K) {
-              A = sg[k];
-              B = sg[H + k];
-            }
-            pack_slot(vf + g, e, A, B, v[g][e]);
+        for (int e = 0; e < E; ++e) {
+          const int p = slot_pos<P, RI>(t, e / RI, e % RI);
+          const int k = (p <= N / 2) ? p : N - p;
+          cpx<T> A = {T(0), T(0)}, B = {T(0), T(0)};
+          if (valid && k <= K) {
+            A = sg[k];
+            B = sg[H + k];
           }
+          pack_slot(vf + g, e, A, B, v[g][e]);
         }
-      xstage_release();
-      if (vf + 2 < NV) dma_pair(vf + 2);
-    } else if (PF) {
-#pragma unroll
-      for (int g = 0; g < 2; ++g)
-        if (g < nf) pack(vf + g, ra[g], rb[g], v[g]);
-#pragma unroll
-      for (int g = 0; g < 2; ++g)
-        if (vf + 2 + g < NV) load_raw(vf + 2 + g, ra[g], rb[g]);
-    } else {
-      // load and pack slot by slot, so that few raw values are live at once
-#pragma unroll
-      for (int g = 0; g < 2; ++g)
-        if (g < nf) {
-#pragma unroll
-          for (int e = 0; e < E; ++e) {
-            cpx<T> A, B;
-            load_raw_slot(vf + g, e, A, B);
-            pack_slot(vf + g, e, A, B, v[g][e]);
-          }
-        }
-    }
+      }
+    xstage_release();
+    if (vf + 2 < NV) dma_pair(vf + 2);
     if (nf == 2) {
       fft_lines<T, P, 1, 2>(v, lds[0], FS, 0, par, t, idx, twi);
     } else {
@@ -543,10 +445,8 @@ k_xstep(const BoxDev* __restrict__ boxes, int box0, const cpx<T>* __restrict__ t
   }
 
   // products and x-forward, NFF fields at a time in the order phi^3, u . grad
-  // phi, T_xx .. T_yz (phi is then dead after the first group, and this order
-  // fits the four-wavefront register budget without spills); the field indices
-  // are compile-time constants, so the products are straight-line code with
-  // no per-element branching
+  // phi, T_xx .. T_yz (phi is then dead after the first group); the field
+  // indices are compile-time constants, so the products are straight-line code
   const T cs = T(csig_d);
   const T h = T(0.5);
   static_assert(RP == first_radix<P, -1>(), "mirrored radix order");
@@ -579,6 +479,131 @@ k_xstep(const BoxDev* __restrict__ boxes, int box0, const cpx<T>* __restrict__ t
       }
     });
   });
+}
+
+// ---------------------------------------------------------------------------
+// The x stage with a wavefront per field: the wavefronts of a workgroup hold the
+// same LW row pairs, wavefront f inverts field f, leaves its physical values in
+// LDS, forms product f from those of the others and transforms it forward.  One
+// chain of two transforms in a thread where k_xstep has 15, and registers for 4
+// to 8 wavefronts a SIMD.  Small grids are bound by that chain (32^3 FP64 box:
+// 16.4 -> 6.3 us; step 37.8 -> 29.0 us).  Large ones are bound by LDS traffic and
+// memory together: the fields' exchange adds to the former, and larger radices,
+// for which the registers are there now, take more away (N = 128: two
+// exchanges a transform, not three; N = 256 in FP32: one).  Steps with k_xstep and
+// now, us: FP64 64^3 48.7 -> 41.2, 96^3 96.4 -> 75.2, 128^3 127 -> 118; FP32 64^3
+// 38.6 -> 33.6, 96^3 65.8 -> 59.0, 128^3 81.4 -> 77.7, 256^3 758 -> 752; 32 boxes of
+// 64^3 FP32 336 -> 322.  With radix 4 throughout, the larger FP32 grids lost: those
+// 32 boxes 349, 128^3 82.8, 256^3 850.  Workgroups that walk over tiles, with or
+// without the next tile's loads in flight, were 2 to 15% slower.
+// ---------------------------------------------------------------------------
+template <typename T, int N>
+struct XPlanSel {
+  using type = Plan<N>;
+};
+template <typename T> struct XPlanSel<T, 64> { using type = PlanT<64, 8, 8, 8>; };
+template <typename T> struct XPlanSel<T, 128> { using type = PlanT<128, 8, 8, 8, 2>; };
+template <> struct XPlanSel<float, 256> { using type = PlanT<256, 16, 16, 16>; };
+template <typename T, int N>
+using XPlan = typename XPlanSel<T, N>::type;
+// FP64 rows of 256 keep the fields in registers (k_xstep): 255 us against 321 on
+// the single-phase 256 x 256 x 257 channel.
+template <typename T, int N>
+constexpr bool kXfield = !(sizeof(T) == 8 && N == 256);
+template <typename T, int N, bool CH = false, bool SP = false>
+__global__ void __launch_bounds__(SP ? 384 : 512)
+k_xfield(const BoxDev* __restrict__ boxes, int box0, const cpx<T>* __restrict__ tw_g, long long xrows, double kxs) {
+  using P = XPlan<T, N>;
+  const BoxDev& bx = boxes[box0 + blockIdx.z];
+  const cpx<T>* __restrict__ yin = static_cast<const cpx<T>*>(bx.bufa);
+  cpx<T>* __restrict__ xout = static_cast<cpx<T>*>(bx.bufb);
+  constexpr int E = P::E, TT = N / E, LW = 64 / TT, K = (N - 1) / 3, H = K + 1;
+  static_assert(TT <= 64 && 64 % TT == 0, "a wavefront holds whole lines");
+  constexpr bool SWZ = P::E == 16;   // the padded rows would leave one workgroup on a CU
+  constexpr int LP = SWZ ? kRowStrideSwz<N> : kRowStride<N>;
+  constexpr int RS = LW * LP > 64 * E ? LW * LP : 64 * E;   // a wavefront's LDS region
+  constexpr int NV = SP ? 3 : 7, NPR = SP ? 6 : 8;
+  constexpr int RI = first_radix<P, 1>(), RO = last_radix<P, -1>();
+  static_assert(last_radix<P, 1>() == first_radix<P, -1>(), "mirrored radix order");
+  const long long ROWS = CH ? xrows : (long long)N * N;
+  __shared__ cpx<T> twf[tw_size<P, -1>()];
+  __shared__ cpx<T> twi[tw_size<P, 1>()];
+  __shared__ cpx<T> lds[NPR][RS];
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int t = lane % TT, line = lane / TT;
+  const long long r0 = ((long long)xcd_tile(blockIdx.x, gridDim.x) * LW + line) * 2;
+  const bool valid = r0 < ROWS;   // ROWS is even: both rows exist
+  using Idx = std::conditional_t<SWZ, IdxLineSwz<N, TT>, IdxLineMajor<N, TT>>;
+  const Idx idx{line * LP};
+  cpx<T>* buf = lds[wv];
+  int par = 0;
+  cpx<T> a[E], b[E];
+  if (wv < NV) {
+    const cpx<T>* src = yin + (long long)(wv <= 3 ? wv : wv - 1) * ROWS * H + (valid ? r0 : 0) * H;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int p = slot_pos<P, RI>(t, e / RI, e % RI);
+      const int k = (p <= N / 2) ? p : N - p;
+      const bool in = valid && k <= K;
+      a[e] = in ? ld_global(src + k) : cpx<T>{T(0), T(0)};
+      b[e] = in ? ld_global(src + H + k) : cpx<T>{T(0), T(0)};
+    }
+  }
+  build_twiddles<T, P, -1>(twf, [&](int m) { return tw_g[m]; }, tid, int(blockDim.x));
+  build_twiddles<T, P, 1>(twi, [&](int m) { return tw_g[m]; }, tid, int(blockDim.x));
+  __syncthreads();
+  cpx<T> v[1][E];
+  if (wv < NV) {
+    const bool dx = wv == 4;   // i kx times phi
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int p = slot_pos<P, RI>(t, e / RI, e % RI);
+      const int k = (p <= N / 2) ? p : N - p;
+      cpx<T> A = a[e], B = b[e];
+      if (dx) {
+        const T kx = CH ? T(double(k) * kxs) : T(k);
+        A = cpx<T>{-kx * A.im, kx * A.re};
+        B = cpx<T>{-kx * B.im, kx * B.re};
+      }
+      if (k == 0) {
+        A.im = T(0);
+        B.im = T(0);
+      }
+      v[0][e] = (p <= N / 2) ? cpx<T>{A.re - B.im, A.im + B.re} : cpx<T>{A.re + B.im, B.re - A.im};
+    }
+    fft_lines<T, P, 1, 1>(v, buf, 0, 0, par, t, idx, twi);
+    wave_lds_sync();   // the exchange's reads, before the values over them
+#pragma unroll
+    for (int e = 0; e < E; ++e) buf[e * 64 + lane] = v[0][e];
+  }
+  __syncthreads();
+  const T cs = T(bx.csig);
+  static_for<0, NPR>([&](auto fc) {
+    constexpr int F = decltype(fc)::value;
+    if (wv == F) {
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        cpx<T> ph[NV][1];
+#pragma unroll
+        for (int g = 0; g < NV; ++g) ph[g][0] = lds[g][e * 64 + lane];
+        v[0][e] = cpx<T>{xproduct<F>(ph, 0, 0, cs), xproduct<F>(ph, 0, 1, cs)};
+      }
+    }
+  });
+  __syncthreads();
+  fft_lines<T, P, -1, 1>(v, buf, 0, 0, par, t, idx, twf);
+  wave_lds_sync();
+  // natural order, then the retained kx of both rows
+#pragma unroll
+  for (int e = 0; e < E; ++e) buf[idx(slot_pos<P, RO>(t, e / RO, e % RO))] = v[0][e];
+  wave_lds_sync();
+  const T h = T(0.5);
+  cpx<T>* dst = xout + (long long)wv * ROWS * H + r0 * H;
+  for (int k = t; valid && k < H; k += TT) {
+    const cpx<T> zk = buf[idx(k)], zm = buf[idx((N - k) % N)];
+    st_global(dst + k, cpx<T>{h * (zk.re + zm.re), h * (zk.im - zm.im)});
+    st_global(dst + H + k, cpx<T>{h * (zk.im + zm.im), h * (zm.re - zk.re)});
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1146,8 +1171,13 @@ hipError_t step_nv(int stage, const BoxDev* boxes, int box0, int nbox, const cpx
     }
     case 1: {  // x stage with products
       const long long pairs = (long long)N * N / 2;
-      const dim3 grid(unsigned((pairs + G::L - 1) / G::L), 1, unsigned(nbox));
-      k_xstep<T, N, V><<<grid, threads, 0, st>>>(boxes, box0, tw, 0, 1.0);
+      if constexpr (kXfield<T, N>) {   // the same workgroups in every variant
+        constexpr int LW = 64 / (N / XPlan<T, N>::E);
+        k_xfield<T, N><<<dim3(unsigned((pairs + LW - 1) / LW), 1, unsigned(nbox)), 512, 0, st>>>(boxes, box0, tw, 0, 1.0);
+      } else {
+        const dim3 grid(unsigned((pairs + G::L - 1) / G::L), 1, unsigned(nbox));
+        k_xstep<T, N, V><<<grid, threads, 0, st>>>(boxes, box0, tw, 0, 1.0);
+      }
       break;
     }
     case 2: {  // y-forward, 8 fields
@@ -1180,11 +1210,18 @@ hipError_t step_n(int stage, int variant, const BoxDev* boxes, int box0, int nbo
 
 template <typename T, int N>
 hipError_t xstage_rows_n(const BoxDev* dev, const cpx<T>* tw, long long rows, double kxs, bool sp, hipStream_t st) {
-  using G = Tile<Plan<N>, 2>;
   const long long pairs = rows / 2;
-  const dim3 grid(unsigned((pairs + G::L - 1) / G::L), 1, 1);
-  if (sp) k_xstep<T, N, 2, true, true><<<grid, unsigned(G::L * G::TT), 0, st>>>(dev, 0, tw, rows, kxs);
-  else k_xstep<T, N, 2, true><<<grid, unsigned(G::L * G::TT), 0, st>>>(dev, 0, tw, rows, kxs);
+  if constexpr (kXfield<T, N>) {
+    constexpr int LW = 64 / (N / XPlan<T, N>::E);
+    const dim3 grid(unsigned((pairs + LW - 1) / LW), 1, 1);
+    if (sp) k_xfield<T, N, true, true><<<grid, 384, 0, st>>>(dev, 0, tw, rows, kxs);
+    else k_xfield<T, N, true><<<grid, 512, 0, st>>>(dev, 0, tw, rows, kxs);
+  } else {
+    using G = Tile<Plan<N>, 2>;
+    const dim3 grid(unsigned((pairs + G::L - 1) / G::L), 1, 1);
+    if (sp) k_xstep<T, N, 2, true, true><<<grid, unsigned(G::L * G::TT), 0, st>>>(dev, 0, tw, rows, kxs);
+    else k_xstep<T, N, 2, true><<<grid, unsigned(G::L * G::TT), 0, st>>>(dev, 0, tw, rows, kxs);
+  }
   return hipGetLastError();
 }
 

@@ -116,7 +116,7 @@ struct PlanT {
 // stage of the latter has 1.5 or 0.75 butterflies per thread, so a quarter of
 // its butterfly slots idle; it takes the place of two or three radix-2 stages,
 // whose exchanges cost more (a stage is one LDS round trip).  Measured at 96^3
-// MIXED against radices 3, 2, 2, 2, 2, 2: x stage 32.6 -> 23.1 us, z 26.1 ->
+// MIXED against radices 3, 2, 2, 2, 2, 2 (with k_xstep): x stage 32.6 -> 23.1 us, z 26.1 ->
 // 22.4, y 12.3 / 10.5 -> 10.7 / 9.3.
 template <int N> struct PlanSel;
 template <> struct PlanSel<8>   { using type = PlanT<8, 4, 4, 2>; };
@@ -197,8 +197,37 @@ __device__ __forceinline__ void dft(cpx<T>* v) {
       v[r] = cadd(a[r], b[r]);
       v[r + 4] = csub(a[r], b[r]);
     }
+  } else if constexpr (R == 16) {
+    // 4 x 4: n = 4 n1 + n2, k = k1 + 4 k2, twiddles exp(S 2 pi i n2 k1 / 16) between
+    const T c = T(0.92387953251128675612818318939679), s = T(S) * T(0.38268343236508977172845998403040);
+    const T h = T(0.70710678118654752440084436210485);
+    cpx<T> a[4][4];
+#pragma unroll
+    for (int n2 = 0; n2 < 4; ++n2) {
+#pragma unroll
+      for (int n1 = 0; n1 < 4; ++n1) a[n2][n1] = v[4 * n1 + n2];
+      dft<4, S>(a[n2]);
+    }
+    auto rot = [](cpx<T> x, T wr, T wi) { return cpx<T>{wr * x.re - wi * x.im, wr * x.im + wi * x.re}; };
+    const T hs = T(S) * h;
+    a[1][1] = rot(a[1][1], c, s);
+    a[1][2] = rot(a[1][2], h, hs);
+    a[1][3] = rot(a[1][3], T(S) * s, T(S) * c);
+    a[2][1] = rot(a[2][1], h, hs);
+    a[2][2] = mul_si<S>(a[2][2]);
+    a[2][3] = rot(a[2][3], -h, hs);
+    a[3][1] = rot(a[3][1], T(S) * s, T(S) * c);
+    a[3][2] = rot(a[3][2], -h, hs);
+    a[3][3] = rot(a[3][3], -c, -s);
+#pragma unroll
+    for (int k1 = 0; k1 < 4; ++k1) {
+      cpx<T> b[4] = {a[0][k1], a[1][k1], a[2][k1], a[3][k1]};
+      dft<4, S>(b);
+#pragma unroll
+      for (int k2 = 0; k2 < 4; ++k2) v[k1 + 4 * k2] = b[k2];
+    }
   } else {
-    static_assert(R == 4, "radix 2, 3, 4, 6 or 8");
+    static_assert(R == 4, "radix 2, 3, 4, 6, 8 or 16");
     const cpx<T> t0 = cadd(v[0], v[2]);
     const cpx<T> t1 = csub(v[0], v[2]);
     const cpx<T> t2 = cadd(v[1], v[3]);

@@ -9,7 +9,7 @@
 //   k_ystep<-1>  y-forward with 2/3 truncation
 //   k_zstep      z-forward, spectral RHS assembly, Leray projection, CN/AB2
 //                (NS) and IE/AB2 (CH) updates, then the z-inverse of the new
-//                state for the next step.
+//                state for the next step (k_zfield: few lines).
 // Spectral data is stored only inside the retained band |k_i| <= K =
 // floor((N-1)/3), so the transforms never read or write discarded modes.
 //
@@ -607,6 +607,95 @@ k_xfield(const BoxDev* __restrict__ boxes, int box0, const cpx<T>* __restrict__ 
 }
 
 // ---------------------------------------------------------------------------
+// The spectral update of one mode, shared by the two z kernels: a box gives the same
+// bits whichever runs it, so every product that is added to is an explicit fma.
+// ---------------------------------------------------------------------------
+// s += i k w
+__device__ __forceinline__ void add_ik(cpx<double>& s, double k, cpx<double> w) {
+  s.re = __builtin_fma(-k, w.im, s.re);
+  s.im = __builtin_fma(k, w.re, s.im);
+}
+// product f's contribution (x: its transform at the mode) to S = (Sx, Sy, Sz, Sp); in
+// the order f = 0 .. 7
+template <int f>
+__device__ __forceinline__ void add_product(cpx<double> (&S)[4], cpx<double> x, double kx, double ky, double kz,
+                                            double k2, const StepCoef& sc) {
+  const cpx<double> w = {x.re * sc.inv_n3, x.im * sc.inv_n3};
+  if constexpr (f == 0) add_ik(S[0], kx, w);                 // d_x T_xx
+  else if constexpr (f == 1) add_ik(S[1], ky, w);            // d_y T_yy
+  else if constexpr (f == 2) add_ik(S[2], kz, w);            // d_z T_zz
+  else if constexpr (f == 3) {                               // T_xy
+    add_ik(S[0], ky, w);
+    add_ik(S[1], kx, w);
+  } else if constexpr (f == 4) {                             // T_xz
+    add_ik(S[0], kz, w);
+    add_ik(S[2], kx, w);
+  } else if constexpr (f == 5) {                             // T_yz
+    add_ik(S[1], kz, w);
+    add_ik(S[2], ky, w);
+  } else if constexpr (f == 6) {                             // -u.grad(phi)
+    S[3].re = __builtin_fma(-sc.inv_n3, x.re, S[3].re);
+    S[3].im = __builtin_fma(-sc.inv_n3, x.im, S[3].im);
+  } else {                                                   // lap(phi^3) / Pe
+    const double c = k2 * sc.inv_pe;
+    S[3].re = __builtin_fma(-c, w.re, S[3].re);
+    S[3].im = __builtin_fma(-c, w.im, S[3].im);
+  }
+}
+// projection, history and the implicit steps of the mode at `id` of the arrays state
+// and hist (M entries a component): S -> the terms kept in hist, u -> the new state.
+// old_state(c), old_hist(c): the values before (old_hist not called for ab1).
+template <class State, class Hist>
+__device__ __forceinline__ void mode_update(cpx<double> (&S)[4], cpx<double> (&u)[4], const State& old_state,
+                                            const Hist& old_hist, cpx<double>* state, cpx<double>* hist, long long M,
+                                            long long id, double kx, double ky, double kz, double k2,
+                                            const StepCoef& sc, cpx<double>* sphi0) {
+  auto fma = [](double a, double b, double c) { return __builtin_fma(a, b, c); };
+  const double ec = sc.e_coef * k2;
+  const cpx<double> ph = old_state(3);
+  S[3].re = fma(ec, ph.re, S[3].re);
+  S[3].im = fma(ec, ph.im, S[3].im);
+  if (k2 == 0.0) {
+    if (sphi0) st_global(sphi0, S[3]);   // the mean of S_phi, a divergence: rounding level
+#pragma unroll
+    for (int c = 0; c < 4; ++c) S[c] = cpx<double>{0.0, 0.0};
+  } else {  // Leray projection
+    const double ir = 1.0 / k2;
+    const double kdr = fma(kz, S[2].re, fma(ky, S[1].re, kx * S[0].re));
+    const double kdi = fma(kz, S[2].im, fma(ky, S[1].im, kx * S[0].im));
+    const double k[3] = {kx, ky, kz};
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      S[c].re = fma(-(k[c] * kdr), ir, S[c].re);
+      S[c].im = fma(-(k[c] * kdi), ir, S[c].im);
+    }
+  }
+  cpx<double> ex[4] = {S[0], S[1], S[2], S[3]};
+  if (!sc.ab1) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const cpx<double> hp = old_hist(c);
+      ex[c] = cpx<double>{fma(1.5, S[c].re, -0.5 * hp.re), fma(1.5, S[c].im, -0.5 * hp.im)};
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < 4; ++c) st_global(hist + c * M + id, S[c]);
+  const double a = 0.5 * sc.dt * sc.nu * k2;
+  const double ia = 1.0 / (1.0 + a), b = 1.0 - a;
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    const cpx<double> o = old_state(c);
+    u[c] = cpx<double>{fma(sc.dt, ex[c].re, b * o.re) * ia, fma(sc.dt, ex[c].im, b * o.im) * ia};
+    st_global(state + c * M + id, u[c]);
+  }
+  const double den = 1.0 / fma(sc.dt * sc.ch2_pe, fma(k2, k2, sc.s * k2), 1.0);
+  u[3] = cpx<double>{fma(sc.dt, ex[3].re, ph.re) * den, fma(sc.dt, ex[3].im, ph.im) * den};
+  st_global(state + 3 * M + id, u[3]);
+}
+// kx^2 + ky^2 + kz^2 of integers: exact in any order
+__device__ __forceinline__ double k_sq(double kx, double ky, double kz) { return kx * kx + ky * ky + kz * kz; }
+
+// ---------------------------------------------------------------------------
 // fused z stage: z-forward of the 8 products, RHS, projection, update, and the
 // z-inverse of the new state.  One line per retained (ky, kx) pair q; each
 // thread keeps the modes its forward transform leaves in registers, which are
@@ -690,29 +779,10 @@ __global__ void __launch_bounds__(64 << V) k_zstep(const BoxDev* __restrict__ bo
 #pragma unroll
       for (int e = 0; e < E; ++e) {
         if (inb[e]) {
-          const cpx<double> w = {double(v[e].re) * sc.inv_n3, double(v[e].im) * sc.inv_n3};
-          const cpx<double> ikx = {-kx * w.im, kx * w.re};
-          const cpx<double> iky = {-ky * w.im, ky * w.re};
-          const cpx<double> ikz = {-kz[e] * w.im, kz[e] * w.re};
-          if constexpr (f == 0) acc[0][e] = cadd(acc[0][e], ikx);                 // d_x T_xx
-          else if constexpr (f == 1) acc[1][e] = cadd(acc[1][e], iky);            // d_y T_yy
-          else if constexpr (f == 2) acc[2][e] = cadd(acc[2][e], ikz);            // d_z T_zz
-          else if constexpr (f == 3) {                                             // T_xy
-            acc[0][e] = cadd(acc[0][e], iky);
-            acc[1][e] = cadd(acc[1][e], ikx);
-          } else if constexpr (f == 4) {                                           // T_xz
-            acc[0][e] = cadd(acc[0][e], ikz);
-            acc[2][e] = cadd(acc[2][e], ikx);
-          } else if constexpr (f == 5) {                                           // T_yz
-            acc[1][e] = cadd(acc[1][e], ikz);
-            acc[2][e] = cadd(acc[2][e], iky);
-          } else if constexpr (f == 6) {                                           // -u.grad(phi)
-            acc[3][e] = csub(acc[3][e], w);
-          } else {                                                                 // lap(phi^3) / Pe
-            const double k2 = kx * kx + ky * ky + kz[e] * kz[e];
-            acc[3][e].re -= k2 * sc.inv_pe * w.re;
-            acc[3][e].im -= k2 * sc.inv_pe * w.im;
-          }
+          cpx<double> S[4] = {acc[0][e], acc[1][e], acc[2][e], acc[3][e]};
+          add_product<f>(S, cpx<double>{double(v[e].re), double(v[e].im)}, kx, ky, kz[e], k_sq(kx, ky, kz[e]), sc);
+#pragma unroll
+          for (int c = 0; c < 4; ++c) acc[c][e] = S[c];
         }
       }
     };
@@ -732,50 +802,13 @@ __global__ void __launch_bounds__(64 << V) k_zstep(const BoxDev* __restrict__ bo
 #pragma unroll
     for (int e = 0; e < E; ++e) {
       if (inb[e]) {
-        const double k2 = kx * kx + ky * ky + kz[e] * kz[e];
         const long long id = (long long)slot[e] * Q + q;
-        cpx<double> Sx = acc[0][e], Sy = acc[1][e], Sz = acc[2][e], Sp = acc[3][e];
-        const cpx<double> ph = ld_global(state + 3 * M + id);
-        Sp.re += sc.e_coef * k2 * ph.re;
-        Sp.im += sc.e_coef * k2 * ph.im;
-        if (k2 == 0.0) {
-          if (bx.sphi0) st_global(bx.sphi0, Sp);   // the mean of S_phi, a divergence: rounding level
-          Sx = Sy = Sz = Sp = cpx<double>{0.0, 0.0};
-        } else {  // Leray projection
-          const double ir = 1.0 / k2;
-          const double kze = kz[e];
-          const cpx<double> kd = {kx * Sx.re + ky * Sy.re + kze * Sz.re, kx * Sx.im + ky * Sy.im + kze * Sz.im};
-          Sx.re -= kx * kd.re * ir; Sx.im -= kx * kd.im * ir;
-          Sy.re -= ky * kd.re * ir; Sy.im -= ky * kd.im * ir;
-          Sz.re -= kze * kd.re * ir; Sz.im -= kze * kd.im * ir;
-        }
-        cpx<double> ex[4] = {Sx, Sy, Sz, Sp};
-        if (!sc.ab1) {
+        cpx<double> S[4] = {acc[0][e], acc[1][e], acc[2][e], acc[3][e]}, u[4];
+        mode_update(
+            S, u, [&](int c) { return ld_global(state + c * M + id); }, [&](int c) { return ld_global(hist + c * M + id); },
+            state, hist, M, id, kx, ky, kz[e], k_sq(kx, ky, kz[e]), sc, bx.sphi0);
 #pragma unroll
-          for (int c = 0; c < 4; ++c) {
-            const cpx<double> hp = ld_global(hist + c * M + id);
-            ex[c].re = 1.5 * ex[c].re - 0.5 * hp.re;
-            ex[c].im = 1.5 * ex[c].im - 0.5 * hp.im;
-          }
-        }
-        st_global(hist + 0 * M + id, Sx);
-        st_global(hist + 1 * M + id, Sy);
-        st_global(hist + 2 * M + id, Sz);
-        st_global(hist + 3 * M + id, Sp);
-        const double a = 0.5 * sc.dt * sc.nu * k2;
-        const double ia = 1.0 / (1.0 + a);
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-          const cpx<double> u = ld_global(state + c * M + id);
-          const cpx<double> un = {((1.0 - a) * u.re + sc.dt * ex[c].re) * ia,
-                                  ((1.0 - a) * u.im + sc.dt * ex[c].im) * ia};
-          st_global(state + c * M + id, un);
-          acc[c][e] = un;
-        }
-        const double den = 1.0 / (1.0 + sc.dt * sc.ch2_pe * (k2 * k2 + sc.s * k2));
-        const cpx<double> pn = {(ph.re + sc.dt * ex[3].re) * den, (ph.im + sc.dt * ex[3].im) * den};
-        st_global(state + 3 * M + id, pn);
-        acc[3][e] = pn;
+        for (int c = 0; c < 4; ++c) acc[c][e] = u[c];
       }
     }
   } else {
@@ -820,6 +853,127 @@ __global__ void __launch_bounds__(64 << V) k_zstep(const BoxDev* __restrict__ bo
   inv_fields(integral_constant<int, 0>(), integral_constant<int, 2>());
   inv_fields(integral_constant<int, 2>(), integral_constant<int, 2>());
   inv_fields(integral_constant<int, 4>(), integral_constant<int, 1>());
+}
+
+// ---------------------------------------------------------------------------
+// The z stage with a group of threads per field: group f transforms product f of
+// L lines forward and leaves the band's modes in LDS; the modes are then updated one
+// to a thread; group f < 5 inverts the new state's field f.  One line set of a small
+// grid leaves k_zstep with a few workgroups (8 at 32^3), each a chain of 13 transforms
+// and, per thread, E modes' updates: 15 us at 32^3, where this takes 5.  Steps with
+// k_zstep and with it, us: FP64 32^3 28.0 -> 19.4, 48^3 37.6 -> 24.6, 64^3 41.0 -> 34.1,
+// 96^3 75.3 -> 71.2; FP32 32^3 25.3 -> 18.0, 64^3 33.2 -> 28.0, 96^3 58.6 -> 50.3.
+// ---------------------------------------------------------------------------
+// lines of a workgroup: 64-byte rows
+template <typename T>
+constexpr int kZlines = 64 / int(sizeof(cpx<T>));
+// The most lines (over all boxes) of a launch for which it runs.  Beyond, the chip is
+// full and its barriers and LDS passes cost more than they save: FP64 16 and 32 boxes of
+// 32^3 (3696, 7392 lines) 51 and 80 us against 55 and 78, 4 and 16 of 48^3 (1984, 7936)
+// 48 and 116 against 60 and 107, 4 of 64^3 (3784) 72 against 69; FP32 4 of 64^3 54
+// against 52, 1 and 4 of 96^3 (2016, 8064) 50 and 130 against 59 and 115.
+template <typename T, int N>
+constexpr int kZfieldMost = N > 96 ? 0 : N >= (sizeof(T) == 8 ? 48 : 64) ? 2048 : 4096;
+template <typename T, int N>
+constexpr int kZthreads = 8 * (N / Plan<N>::E) * kZlines<T>;
+template <typename T, int N>
+__global__ void __launch_bounds__((kZthreads<T, N>))
+k_zfield(const BoxDev* __restrict__ boxes, int box0, const cpx<T>* __restrict__ tw_g, int do_update) {
+  using P = Plan<N>;
+  const BoxDev& bx = boxes[box0 + blockIdx.z];
+  const cpx<T>* __restrict__ rhs = static_cast<const cpx<T>*>(bx.bufa);
+  cpx<double>* __restrict__ state = bx.state;
+  cpx<double>* __restrict__ hist = bx.hist;
+  cpx<T>* __restrict__ gout = static_cast<cpx<T>*>(bx.bufb);
+  const StepCoef sc = bx.sc;
+  constexpr int E = P::E, TT = N / E, L = kZlines<T>, K = (N - 1) / 3, C = 2 * K + 1, H = K + 1;
+  constexpr int Q = C * H, THREADS = kZthreads<T, N>;
+  constexpr long long M = (long long)C * Q;
+  constexpr int RF = first_radix<P, -1>(), RL = last_radix<P, -1>();
+  static_assert(RL == first_radix<P, 1>(), "mirrored radix order");
+  static_assert(C * L <= THREADS && THREADS <= 1024, "a mode per thread");
+  __shared__ cpx<T> tw[N];
+  __shared__ cpx<T> lds[2][8][N * L];
+  const int tid = threadIdx.x;
+  const int line = tid % L, t = tid / L % TT, f = tid / (L * TT);
+  const int q = xcd_tile(blockIdx.x, gridDim.x) * L + line;
+  const bool valid = q < Q;
+  cpx<T> v[1][E];
+  if (do_update) {
+    const cpx<T>* src = rhs + (long long)f * N * Q + (valid ? q : 0);
+#pragma unroll
+    for (int b = 0; b < E / RF; ++b)
+#pragma unroll
+      for (int r = 0; r < RF; ++r) v[0][b * RF + r] = ld_global(src + (long long)slot_pos<P, RF>(t, b, r) * Q);
+  }
+  // the mode that this thread updates
+  const int slot = tid / L;
+  const bool mode = valid && slot < C;
+  const long long id = (long long)(mode ? slot : 0) * Q + (mode ? q : 0);
+  cpx<double> u[4], hp[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    u[c] = ld_global(state + c * M + id);
+    hp[c] = cpx<double>{0.0, 0.0};
+    if (do_update && !sc.ab1) hp[c] = ld_global(hist + c * M + id);
+  }
+  for (int i = tid; i < N; i += THREADS) tw[i] = tw_g[i];
+  const IdxPosSwz idx{L, line};
+  int par = 0;
+  __syncthreads();
+  const int iy = valid ? q / H : 0, ix = valid ? q % H : 0;
+  const double kx = double(ix), ky = double(iy <= K ? iy : iy - C), kz = double(slot <= K ? slot : slot - C);
+  if (do_update) {
+    fft_lines<T, P, -1, 1>(v, lds[0][f], 0, 8 * N * L, par, t, idx, tw);
+    __syncthreads();   // the exchanges' reads, before the modes over them
+#pragma unroll
+    for (int b = 0; b < E / RL; ++b)
+#pragma unroll
+      for (int r = 0; r < RL; ++r) {
+        const int s = band_slot(slot_pos<P, RL>(t, b, r), C, N);
+        if (s >= 0) lds[0][f][s * L + line] = v[0][b * RL + r];
+      }
+    __syncthreads();
+  }
+  if (mode) {
+    if (do_update) {
+      cpx<double> S[4] = {};
+      const double k2 = k_sq(kx, ky, kz);
+      static_for<0, 8>([&](auto fc) {
+        constexpr int g = decltype(fc)::value;
+        const cpx<T> x = lds[0][g][slot * L + line];
+        add_product<g>(S, cpx<double>{double(x.re), double(x.im)}, kx, ky, kz, k2, sc);
+      });
+      cpx<double> un[4];
+      mode_update(
+          S, un, [&](int c) { return u[c]; }, [&](int c) { return hp[c]; }, state, hist, M, id, kx, ky, kz, k2, sc,
+          bx.sphi0);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) u[c] = un[c];
+    }
+    const cpx<double> kp = {-kz * u[3].im, kz * u[3].re};
+#pragma unroll
+    for (int c = 0; c < 5; ++c) lds[1][c][slot * L + line] = to_cpx<T>(c < 4 ? u[c] : kp);
+  }
+  __syncthreads();
+  // z-inverse of u, v, w, phi and i kz phi (groups 5 .. 7 only keep the barriers)
+#pragma unroll
+  for (int b = 0; b < E / RL; ++b)
+#pragma unroll
+    for (int r = 0; r < RL; ++r) {
+      const int s = band_slot(slot_pos<P, RL>(t, b, r), C, N);
+      v[0][b * RL + r] = (valid && f < 5 && s >= 0) ? lds[1][f][s * L + line] : cpx<T>{T(0), T(0)};
+    }
+  __syncthreads();
+  par = 0;
+  fft_lines<T, P, 1, 1>(v, lds[0][f], 0, 8 * N * L, par, t, idx, tw);
+  if (valid && f < 5) {
+    cpx<T>* dst = gout + (long long)f * N * Q + q;
+#pragma unroll
+    for (int b = 0; b < E / RF; ++b)
+#pragma unroll
+      for (int r = 0; r < RF; ++r) st_global(dst + (long long)slot_pos<P, RF>(t, b, r) * Q, v[0][b * RF + r]);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1188,6 +1342,14 @@ hipError_t step_nv(int stage, const BoxDev* boxes, int box0, int nbox, const cpx
     }
     default: {  // z stage with the update
       const int Q = G::C * G::H;
+      if constexpr (kZfieldMost<T, N> > 0) {
+        if ((long long)Q * nbox <= kZfieldMost<T, N>) {   // the same workgroups in every variant
+          constexpr int L = kZlines<T>;
+          k_zfield<T, N><<<dim3(unsigned((Q + L - 1) / L), 1, unsigned(nbox)), kZthreads<T, N>, 0, st>>>(boxes, box0, tw,
+                                                                                                       do_update);
+          break;
+        }
+      }
       const dim3 grid(unsigned((Q + G::L - 1) / G::L), 1, unsigned(nbox));
       k_zstep<T, N, V><<<grid, threads, 0, st>>>(boxes, box0, tw, do_update);
       break;

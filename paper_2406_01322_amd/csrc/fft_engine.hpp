@@ -37,14 +37,19 @@ template <typename T>
 __device__ __forceinline__ cpx<T> cadd(cpx<T> a, cpx<T> b) { return {a.re + b.re, a.im + b.im}; }
 template <typename T>
 __device__ __forceinline__ cpx<T> csub(cpx<T> a, cpx<T> b) { return {a.re - b.re, a.im - b.im}; }
+// The products of a transform that are added to are explicit fused multiply-adds
+// (here and in dft): left to the compiler, which of them it fuses depends on the
+// kernel around them, and so would the bits.
+__device__ __forceinline__ float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
 template <typename T>
 __device__ __forceinline__ cpx<T> cmul(cpx<T> a, cpx<T> b) {
-  return {a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re};
+  return {fma_t(a.re, b.re, -(a.im * b.im)), fma_t(a.re, b.im, a.im * b.re)};
 }
 // a * conj(b)
 template <typename T>
 __device__ __forceinline__ cpx<T> cmulc(cpx<T> a, cpx<T> b) {
-  return {a.re * b.re + a.im * b.im, a.im * b.re - a.re * b.im};
+  return {fma_t(a.re, b.re, a.im * b.im), fma_t(a.im, b.re, -(a.re * b.im))};
 }
 // a * (S i)
 template <int S, typename T>
@@ -167,11 +172,10 @@ __device__ __forceinline__ void dft(cpx<T>* v) {
     const T c2 = T(S) * T(0.86602540378443864676372317075294);
     const cpx<T> s = cadd(v[1], v[2]);
     const cpx<T> d = csub(v[1], v[2]);
-    const cpx<T> m = {v[0].re + c1 * s.re, v[0].im + c1 * s.im};
-    const cpx<T> r = {-c2 * d.im, c2 * d.re};
+    const cpx<T> m = {fma_t(c1, s.re, v[0].re), fma_t(c1, s.im, v[0].im)};
     v[0] = cadd(v[0], s);
-    v[1] = cadd(m, r);
-    v[2] = csub(m, r);
+    v[1] = cpx<T>{fma_t(-c2, d.im, m.re), fma_t(c2, d.re, m.im)};
+    v[2] = cpx<T>{fma_t(c2, d.im, m.re), fma_t(-c2, d.re, m.im)};
   } else if constexpr (R == 6) {
     // prime factors 2 x 3: n = 3 n1 + 2 n2, k = 3 k1 + 4 k2 (mod 6), no twiddles
     cpx<T> a[3] = {v[0], v[2], v[4]}, b[3] = {v[3], v[5], v[1]};
@@ -188,14 +192,20 @@ __device__ __forceinline__ void dft(cpx<T>* v) {
     cpx<T> a[4] = {v[0], v[2], v[4], v[6]}, b[4] = {v[1], v[3], v[5], v[7]};
     dft<4, S>(a);
     dft<4, S>(b);
-    // times exp(S 2 pi i r / 8)
-    b[1] = cpx<T>{h * (b[1].re - T(S) * b[1].im), h * (b[1].im + T(S) * b[1].re)};
+    // times exp(S 2 pi i r / 8): b[1] and b[3] over sqrt(1/2), which the last sums apply
+    const cpx<T> sb1 = mul_si<S>(b[1]), sb3 = mul_si<S>(b[3]);
+    b[1] = cadd(b[1], sb1);
     b[2] = mul_si<S>(b[2]);
-    b[3] = cpx<T>{-h * (b[3].re + T(S) * b[3].im), h * (T(S) * b[3].re - b[3].im)};
+    b[3] = csub(sb3, b[3]);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      v[r] = cadd(a[r], b[r]);
-      v[r + 4] = csub(a[r], b[r]);
+      if (r % 2) {
+        v[r] = cpx<T>{fma_t(h, b[r].re, a[r].re), fma_t(h, b[r].im, a[r].im)};
+        v[r + 4] = cpx<T>{fma_t(-h, b[r].re, a[r].re), fma_t(-h, b[r].im, a[r].im)};
+      } else {
+        v[r] = cadd(a[r], b[r]);
+        v[r + 4] = csub(a[r], b[r]);
+      }
     }
   } else if constexpr (R == 16) {
     // 4 x 4: n = 4 n1 + n2, k = k1 + 4 k2, twiddles exp(S 2 pi i n2 k1 / 16) between
@@ -208,7 +218,7 @@ __device__ __forceinline__ void dft(cpx<T>* v) {
       for (int n1 = 0; n1 < 4; ++n1) a[n2][n1] = v[4 * n1 + n2];
       dft<4, S>(a[n2]);
     }
-    auto rot = [](cpx<T> x, T wr, T wi) { return cpx<T>{wr * x.re - wi * x.im, wr * x.im + wi * x.re}; };
+    auto rot = [](cpx<T> x, T wr, T wi) { return cmul(x, cpx<T>{wr, wi}); };
     const T hs = T(S) * h;
     a[1][1] = rot(a[1][1], c, s);
     a[1][2] = rot(a[1][2], h, hs);

@@ -66,6 +66,31 @@ def test_smallest_box_steps(n, precision, tol):
             assert np.linalg.norm(a - b) <= tol * np.linalg.norm(b)
 
 
+# A box alone takes the z stage with a group of threads per field, boxes enough of one
+# size the one with the fields in registers: the same bits (AB1, then AB2 steps).
+@pytest.mark.parametrize("n,boxes", [(12, 92), (16, 63), (24, 35), (32, 18), (48, 9), (64, 5), (96, 2)])
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_z_stages_give_the_same_bits(n, boxes, precision):
+    from paper_2406_01322_amd.psms import Batch, Solver
+    p = dict(n=n, re=50.0, we=1.0, ch=0.2, pe=5.0, dt=1e-3)
+    rng = np.random.default_rng(n)
+    u, phi = rng.standard_normal((3, n, n, n)), rng.standard_normal((n, n, n))
+    s = Solver(precision=precision, **p)
+    s.init_state(_dev(u), _dev(phi))
+    b = Batch([p] * boxes, precision=precision)
+    for i in (0, boxes - 1):
+        b.init_state(i, _dev(u), _dev(phi))
+    for i in range(1, boxes - 1):
+        b.init_state(i, _dev(np.zeros_like(u)), _dev(np.zeros_like(phi)))
+    s.step(3)
+    b.step(3)
+    torch.cuda.synchronize()
+    want = s.get_state()
+    for i in (0, boxes - 1):
+        got = b.get_state(i)
+        assert all(torch.equal(x, y) for x, y in zip(got, want))
+
+
 # Fields are transformed several per launch, in chunks that the scratch holds: more
 # fields than a chunk give each field what it gives alone, bit for bit, with and
 # without the mask pass, and an inverse over its own input the same.

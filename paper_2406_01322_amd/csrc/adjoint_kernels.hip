@@ -137,143 +137,148 @@ __global__ void __launch_bounds__(256) k_zadj_in(cpx<double>* __restrict__ lam, 
 // the y-inverse [8][N][N][H]; out: [7][N][N][H] x-forward of the cotangents
 // of u v w phi gx gy gz.  part[blockIdx.x]: this block's share of
 // sum_x sum_f Tbar_f dT_f/dc (the We term before the factor -c/(We n^3)).
+// A wavefront per field, as in the forward step's x stage: wavefront w of a workgroup
+// inverts forward field w and cotangent w of the same LW row pairs (8 has no forward
+// field) and leaves the physical values in LDS; after the barrier the first seven
+// form and transform one field's cotangent each, and the last sums the We term.  In
+// registers, one thread's 22 transforms and 12 fields left one wavefront a SIMD: 158
+// us at 128^3 against 114 us (worth 46 us of memory traffic: the rest is LDS exchanges and
+// reads at two workgroups a CU).
 template <int N>
-__global__ void __launch_bounds__(256) k_xadj(const cpx<double>* __restrict__ yf, const cpx<double>* __restrict__ yb,
+struct AdjTile {
+  using P = Plan<N>;
+  static constexpr int E = P::E, TT = N / E, LW = 64 / TT, K = (N - 1) / 3, H = K + 1;
+  static constexpr bool SWZ = N % 16 == 0;
+  static constexpr int LP = SWZ ? kRowStrideSwz<N> : kRowStride<N>;
+  static constexpr int RS = LW * LP > 64 * E ? LW * LP : 64 * E;   // a field's LDS region
+  static_assert(TT <= 64 && 64 % TT == 0, "a wavefront holds whole lines");
+  static constexpr int blocks() { return int(((long long)N * N / 2 + LW - 1) / LW); }
+};
+template <int N>
+__global__ void __launch_bounds__(512) k_xadj(const cpx<double>* __restrict__ yf, const cpx<double>* __restrict__ yb,
                                               cpx<double>* __restrict__ out, const cpx<double>* __restrict__ tw_g,
                                               double csig, double* __restrict__ part) {
   using P = Plan<N>;
-  using G = Tile<P>;
-  constexpr int E = G::E, TT = G::TT, L = G::L, LP = kRowStride<N>, K = G::K, H = G::H;
-  constexpr int RI = first_radix<P, 1>(), RP = last_radix<P, 1>(), RO = last_radix<P, -1>();
-  static_assert(RP == first_radix<P, -1>(), "mirrored radix order");
-  constexpr long long ROWS = (long long)N * N;
+  using A = AdjTile<N>;
+  constexpr int E = A::E, TT = A::TT, LW = A::LW, K = A::K, H = A::H, RS = A::RS;
+  constexpr int RI = first_radix<P, 1>(), RO = last_radix<P, -1>();
+  static_assert(last_radix<P, 1>() == first_radix<P, -1>(), "mirrored radix order");
+  constexpr long long ROWS = (long long)N * N, FS = ROWS * H;
   __shared__ cpx<double> twf[tw_size<P, -1>()];
   __shared__ cpx<double> twi[tw_size<P, 1>()];
-  __shared__ cpx<double> lds[2][L * LP];
-  __shared__ double red[256];
-  const int tid = threadIdx.x;
-  const int t = tid % TT, line = tid / TT;
+  __shared__ cpx<double> lds[15][RS];   // u v w gx gy gz phi, then the 8 cotangents
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int t = lane % TT, line = lane / TT;
+  const long long r0 = ((long long)xcd_tile(blockIdx.x, gridDim.x) * LW + line) * 2;
+  const bool valid = r0 < ROWS;   // ROWS is even: both rows exist
+  using Idx = std::conditional_t<A::SWZ, IdxLineSwz<N, TT>, IdxLineMajor<N, TT>>;
+  const Idx idx{line * A::LP};
+  const bool dx = wv == 3;        // gx = i kx phi
+  const cpx<double>* sf = yf + (wv < 3 ? wv : wv == 4 ? 4 : wv == 5 ? 5 : 3) * FS + (valid ? r0 : 0) * H;
+  const cpx<double>* sb = yb + wv * FS + (valid ? r0 : 0) * H;
+  cpx<double> v[2][E];
+  // the packed complex line row0 + i row1 of both fields in Hermitian-extended order
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int p = slot_pos<P, RI>(t, e / RI, e % RI);
+    const int k = (p <= N / 2) ? p : N - p;
+    const bool in = valid && k <= K;
+    const cpx<double> zero = {0.0, 0.0};
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+      const cpx<double>* src = g ? sb : sf;
+      cpx<double> a = in ? src[k] : zero, b = in ? src[H + k] : zero;
+      if (g == 0 && dx) {
+        const double kk = double(k);
+        a = cpx<double>{-kk * a.im, kk * a.re};
+        b = cpx<double>{-kk * b.im, kk * b.re};
+      }
+      if (k == 0) {
+        a.im = 0.0;
+        b.im = 0.0;
+      }
+      v[g][e] = (p <= N / 2) ? cpx<double>{a.re - b.im, a.im + b.re} : cpx<double>{a.re + b.im, b.re - a.im};
+    }
+  }
   build_twiddles<double, P, -1>(twf, [&](int m) { return tw_g[m]; }, tid, int(blockDim.x));
   build_twiddles<double, P, 1>(twi, [&](int m) { return tw_g[m]; }, tid, int(blockDim.x));
-  const long long r0 = ((long long)blockIdx.x * L + line) * 2;
-  const bool valid = r0 < ROWS;
-  const IdxLineMajor<N, TT> idx{line * LP};
-  int par = 0;
   __syncthreads();
-
-  // x-inverse of one field of a [*][N][N][H] array into register slots (re: row r0, im: row r0+1)
-  auto xinv = [&](const cpx<double>* src, bool dx, cpx<double>* v) {
+  int par = 0;
+  if (wv < 7) {
+    fft_lines<double, P, 1, 2>(v, lds[wv], 7 * RS, 0, par, t, idx, twi);
+    wave_lds_sync();   // the exchange's reads, before the values over them
 #pragma unroll
-    for (int b = 0; b < E / RI; ++b)
-#pragma unroll
-      for (int r = 0; r < RI; ++r) {
-        const int p = slot_pos<P, RI>(t, b, r);
-        const int k = (p <= N / 2) ? p : N - p;
-        cpx<double> z = {0.0, 0.0};
-        if (valid && k <= K) {
-          cpx<double> A = src[r0 * H + k], B = src[(r0 + 1) * H + k];
-          if (dx) {
-            const double kk = double(k);
-            A = cpx<double>{-kk * A.im, kk * A.re};
-            B = cpx<double>{-kk * B.im, kk * B.re};
-          }
-          if (k == 0) {
-            A.im = 0.0;
-            B.im = 0.0;
-          }
-          z = (p <= N / 2) ? cpx<double>{A.re - B.im, A.im + B.re} : cpx<double>{A.re + B.im, B.re - A.im};
-        }
-        v[b * RI + r] = z;
-      }
-    fft_line<double, P, 1>(v, lds[0], lds[1], par, t, idx, twi);
-  };
-  // x-forward of register slots and store of the retained kx of both rows
-  auto xfwd = [&](cpx<double>* v, cpx<double>* dst) {
-    fft_line<double, P, -1>(v, lds[0], lds[1], par, t, idx, twf);
-    cpx<double>* Lb = par ? lds[1] : lds[0];
-    par ^= 1;
-#pragma unroll
-    for (int b = 0; b < E / RO; ++b)
-#pragma unroll
-      for (int r = 0; r < RO; ++r) Lb[idx(slot_pos<P, RO>(t, b, r))] = v[b * RO + r];
-    wave_lds_sync();  // the line's threads are one wavefront's lanes
-    for (int k = t; valid && k < H; k += TT) {
-      const cpx<double> zk = Lb[idx(k)], zm = Lb[idx((N - k) % N)];
-      dst[r0 * H + k] = cpx<double>{0.5 * (zk.re + zm.re), 0.5 * (zk.im - zm.im)};
-      dst[(r0 + 1) * H + k] = cpx<double>{0.5 * (zk.im + zm.im), 0.5 * (zm.re - zk.re)};
-    }
-  };
-  const long long FS = ROWS * H;
-
-  // phi: phi_bar = 3 phi^2 c_bar
-  {
-    cpx<double> ph[E], cb[E];
-    xinv(yf + 3 * FS, false, ph);
-    xinv(yb + 7 * FS, false, cb);
-#pragma unroll
-    for (int e = 0; e < E; ++e) cb[e] = cpx<double>{3.0 * ph[e].re * ph[e].re * cb[e].re, 3.0 * ph[e].im * ph[e].im * cb[e].im};
-    xfwd(cb, out + 3 * FS);
+    for (int e = 0; e < E; ++e) lds[wv][e * 64 + lane] = v[0][e];
+  } else {
+    fft_lines<double, P, 1, 1>(v + 1, lds[14], 0, 0, par, t, idx, twi);
+    wave_lds_sync();
   }
-  // forward fields u v w gx gy gz
-  cpx<double> fw[6][E];
-  xinv(yf + 0 * FS, false, fw[0]);
-  xinv(yf + 1 * FS, false, fw[1]);
-  xinv(yf + 2 * FS, false, fw[2]);
-  xinv(yf + 3 * FS, true, fw[3]);
-  xinv(yf + 4 * FS, false, fw[4]);
-  xinv(yf + 5 * FS, false, fw[5]);
-  cpx<double> acc[6][E];
 #pragma unroll
-  for (int c = 0; c < 6; ++c)
-#pragma unroll
-    for (int e = 0; e < E; ++e) acc[c][e] = cpx<double>{0.0, 0.0};
-  double dwe = 0.0;
+  for (int e = 0; e < E; ++e) lds[7 + wv][e * 64 + lane] = v[1][e];
+  __syncthreads();
   const double c2 = 2.0 * csig;
+  auto at = [&](int f, int e) { return lds[f][e * 64 + lane]; };
+  // component-wise products of the two rows
+  auto mul = [](cpx<double> a, cpx<double> b) { return cpx<double>{a.re * b.re, a.im * b.im}; };
   static_for<0, 7>([&](auto fc) {
-    constexpr int f = decltype(fc)::value;
-    cpx<double> tb[E];
-    xinv(yb + f * FS, false, tb);
+    constexpr int F = decltype(fc)::value;
+    if (wv == F) {
 #pragma unroll
-    for (int e = 0; e < E; ++e) {
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const double u = h ? fw[0][e].im : fw[0][e].re, v = h ? fw[1][e].im : fw[1][e].re;
-        const double w = h ? fw[2][e].im : fw[2][e].re, gx = h ? fw[3][e].im : fw[3][e].re;
-        const double gy = h ? fw[4][e].im : fw[4][e].re, gz = h ? fw[5][e].im : fw[5][e].re;
-        const double x = h ? tb[e].im : tb[e].re;
-        double du = 0, dv = 0, dw = 0, dgx = 0, dgy = 0, dgz = 0;
-        if constexpr (f == 0) { du = -2.0 * u * x; dgy = c2 * gy * x; dgz = c2 * gz * x; dwe += x * (gy * gy + gz * gz); }
-        else if constexpr (f == 1) { dv = -2.0 * v * x; dgx = c2 * gx * x; dgz = c2 * gz * x; dwe += x * (gx * gx + gz * gz); }
-        else if constexpr (f == 2) { dw = -2.0 * w * x; dgx = c2 * gx * x; dgy = c2 * gy * x; dwe += x * (gx * gx + gy * gy); }
-        else if constexpr (f == 3) { du = -v * x; dv = -u * x; dgx = -csig * gy * x; dgy = -csig * gx * x; dwe -= x * gx * gy; }
-        else if constexpr (f == 4) { du = -w * x; dw = -u * x; dgx = -csig * gz * x; dgz = -csig * gx * x; dwe -= x * gx * gz; }
-        else if constexpr (f == 5) { dv = -w * x; dw = -v * x; dgy = -csig * gz * x; dgz = -csig * gy * x; dwe -= x * gy * gz; }
-        else { du = gx * x; dv = gy * x; dw = gz * x; dgx = u * x; dgy = v * x; dgz = w * x; }
-        if (h) {
-          acc[0][e].im += du; acc[1][e].im += dv; acc[2][e].im += dw;
-          acc[3][e].im += dgx; acc[4][e].im += dgy; acc[5][e].im += dgz;
+      for (int e = 0; e < E; ++e) {
+        auto f = [&](int i) { return at(i, e); };
+        auto x = [&](int i) { return at(7 + i, e); };
+        cpx<double> r;
+        if constexpr (F < 3) {
+          // u: -2 u x0 - v x3 - w x4 + gx x6; v: -2 v x1 - u x3 - w x5 + gy x6; w: ..
+          constexpr int i1 = F == 0 ? 1 : 0, c1 = F == 2 ? 4 : 3, i2 = F == 2 ? 1 : 2, d1 = F == 0 ? 4 : 5;
+          const cpx<double> a = mul(f(F), x(F)), b = mul(f(i1), x(c1)), c = mul(f(i2), x(d1)), d = mul(f(3 + F), x(6));
+          r = cpx<double>{-2.0 * a.re - b.re - c.re + d.re, -2.0 * a.im - b.im - c.im + d.im};
+        } else if constexpr (F == 6) {
+          const cpx<double> ph = f(6), a = mul(mul(ph, ph), x(7));
+          r = cpx<double>{3.0 * a.re, 3.0 * a.im};
         } else {
-          acc[0][e].re += du; acc[1][e].re += dv; acc[2][e].re += dw;
-          acc[3][e].re += dgx; acc[4][e].re += dgy; acc[5][e].re += dgz;
+          // gx: 2c gx (x1 + x2) - c gy x3 - c gz x4 + u x6; gy: 2c gy (x0 + x2) - c gx x3 - c gz x5 + v x6; gz: ..
+          constexpr int g = F - 3, n1 = g == 0 ? 1 : 0, n2 = g == 2 ? 1 : 2;
+          constexpr int i1 = g == 0 ? 4 : 3, c1 = g == 2 ? 4 : 3, i2 = g == 2 ? 4 : 5, d1 = g == 0 ? 4 : 5;
+          const cpx<double> a = mul(f(F), cadd(x(n1), x(n2))), b = mul(f(i1), x(c1)), c = mul(f(i2), x(d1)),
+                            d = mul(f(g), x(6));
+          r = cpx<double>{c2 * a.re - csig * (b.re + c.re) + d.re, c2 * a.im - csig * (b.im + c.im) + d.im};
         }
+        v[0][e] = r;
       }
     }
   });
-  if (!valid) dwe = 0.0;
-  xfwd(acc[0], out + 0 * FS);
-  xfwd(acc[1], out + 1 * FS);
-  xfwd(acc[2], out + 2 * FS);
-  xfwd(acc[3], out + 4 * FS);
-  xfwd(acc[4], out + 5 * FS);
-  xfwd(acc[5], out + 6 * FS);
-  // block reduction of the We term (fixed order: deterministic)
-  red[tid] = dwe;
-  __syncthreads();
-  for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-    if (tid < s) red[tid] += red[tid + s];
-    __syncthreads();
+  if (wv == 7) {
+    double dwe = 0.0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const cpx<double> gx = at(3, e), gy = at(4, e), gz = at(5, e);
+      const cpx<double> xx = mul(gx, gx), yy = mul(gy, gy), zz = mul(gz, gz);
+      const cpx<double> s0 = mul(at(7, e), cadd(yy, zz)), s1 = mul(at(8, e), cadd(xx, zz)), s2 = mul(at(9, e), cadd(xx, yy));
+      const cpx<double> s3 = mul(at(10, e), mul(gx, gy)), s4 = mul(at(11, e), mul(gx, gz)), s5 = mul(at(12, e), mul(gy, gz));
+      const cpx<double> d = csub(cadd(cadd(s0, s1), s2), cadd(cadd(s3, s4), s5));
+      dwe += d.re + d.im;
+    }
+    if (!valid) dwe = 0.0;
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) dwe += __shfl_xor(dwe, d);   // fixed order: deterministic
+    if (lane == 0) part[blockIdx.x] = dwe;
   }
-  if (tid == 0) part[blockIdx.x] = red[0];
+  __syncthreads();
+  if (wv == 7) return;
+  cpx<double>* buf = lds[wv];
+  fft_lines<double, P, -1, 1>(v, buf, 0, 0, par, t, idx, twf);
+  wave_lds_sync();
+  // natural order, then the retained kx of both rows
+#pragma unroll
+  for (int e = 0; e < E; ++e) buf[idx(slot_pos<P, RO>(t, e / RO, e % RO))] = v[0][e];
+  wave_lds_sync();
+  cpx<double>* dst = out + (wv < 3 ? wv : wv == 6 ? 3 : wv + 1) * FS + r0 * H;
+  for (int k = t; valid && k < H; k += TT) {
+    const cpx<double> zk = buf[idx(k)], zm = buf[idx((N - k) % N)];
+    dst[k] = cpx<double>{0.5 * (zk.re + zm.re), 0.5 * (zk.im - zm.im)};
+    dst[H + k] = cpx<double>{0.5 * (zk.im + zm.im), 0.5 * (zm.re - zk.re)};
+  }
 }
 
 // -------------------------------------------------------------------------
@@ -399,8 +404,7 @@ hipError_t adj_n(int stage, cpx<double>* lam, cpx<double>* mu, const cpx<double>
   if (stage == 0) {
     k_zadj_in<N><<<unsigned((Q + G::L - 1) / G::L), threads, 0, st>>>(lam, mu, out, tw, ac);
   } else if (stage == 1) {
-    const long long pairs = (long long)N * N / 2;
-    k_xadj<N><<<unsigned((pairs + G::L - 1) / G::L), threads, 0, st>>>(a, b, out, tw, csig, part);
+    k_xadj<N><<<unsigned(AdjTile<N>::blocks()), 512, 0, st>>>(a, b, out, tw, csig, part);
   } else {
     k_zadj_out<N><<<unsigned((Q + G::L - 1) / G::L), threads, 0, st>>>(a, lam, tw, ac.inv_n3);
   }
@@ -411,7 +415,7 @@ hipError_t adj_n(int stage, cpx<double>* lam, cpx<double>* mu, const cpx<double>
 int adj_xblocks(int n) {
   switch (n) {
 #define PSMS_CASE(NN) \
-  case NN: return int(((long long)NN * NN / 2 + Tile<Plan<NN>>::L - 1) / Tile<Plan<NN>>::L);
+  case NN: return AdjTile<NN>::blocks();
     PSMS_FOR_EACH_N(PSMS_CASE)
 #undef PSMS_CASE
   }

@@ -268,3 +268,25 @@ def test_channel_derivatives_follow_the_state():
     c.step(1)
     for x in (b, c):
         assert all(torch.equal(p, q) for p, q in zip(x.get_state(), want))
+
+
+# The adjoint's x stage, a wavefront per field: 1 to 32 row pairs a wavefront, a partly
+# filled last workgroup (8, 12), padded (8, 12, 24) and swizzled rows.  Against the
+# oracle's adjoint to the bar of the adjoint tests.
+@pytest.mark.parametrize("n", [8, 12, 32, 48, 64])
+def test_adjoint_x_stage(n):
+    from oracle import adjoint as oadj
+    from paper_2406_01322_amd.psms import Adjoint
+    prm = box.Params(n=n, re=50.0, we=1.0, ch=0.2, pe=5.0, dt=1e-3)
+    rng = np.random.default_rng(n)
+    x = 2 * np.pi * np.arange(n) / n
+    z, y, x = np.meshgrid(x, x, x, indexing="ij")
+    u = np.stack([np.sin(x) * np.cos(y) * np.cos(z), -np.cos(x) * np.sin(y) * np.cos(z), 0.3 * np.cos(x + 2 * y)])
+    phi = np.cos(x) * np.sin(y - z) + 0.1 * rng.standard_normal((n, n, n))
+    J0, d0, w0, _ = oadj.gradient(u, phi, prm, 2)
+    a = Adjoint(n, prm.re, prm.we, prm.ch, prm.pe, prm.dt, precision="fp64", max_steps=2, seg_len=1)
+    J = a.forward(_dev(u), _dev(phi), 2)
+    d, w = a.backward()
+    assert abs(J - J0) <= 1e-10 * abs(J0)
+    assert np.linalg.norm(_host(d) - d0) <= 1e-10 * np.linalg.norm(d0)
+    assert abs(w - w0) <= 1e-10 * abs(w0)

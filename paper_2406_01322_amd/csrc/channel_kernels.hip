@@ -235,9 +235,9 @@ __device__ __forceinline__ void dct_stage(const Src& src, int q, int t, long lon
 // both: a workgroup transforms both sides of a pair, one after the other; else
 // each side has a workgroup (blockIdx.y = 2 pair + side).
 template <typename T, int N, class Src>
-__global__ void __launch_bounds__(CTile<Plan<N>>::L * CTile<Plan<N>>::TT) k_dct(Src src, cpx<T>* __restrict__ out, long long nlines, int nfield,
-                                             int both, int dir, long long fstride, const cpx<T>* __restrict__ tw_g,
-                                             cpx<double>* __restrict__ out64, int kz) {
+__global__ void __launch_bounds__(CTile<Plan<N>>::L * CTile<Plan<N>>::TT)
+k_dct(Src src, cpx<T>* __restrict__ out, long long nlines, int nfield, int both, int dir, long long fstride,
+      const cpx<T>* __restrict__ tw_g, cpx<double>* __restrict__ out64, int kz) {
   using P = Plan<N>;
   using G = CTile<P>;
   constexpr int E = G::E, L = G::L, LP = L + 1, TT = G::TT, NC = N / 2;
@@ -328,10 +328,9 @@ __global__ void __launch_bounds__(CTile<Plan<N>>::L * CTile<Plan<N>>::TT) k_dct(
 // starting value.  dir = +1: x = f, a_n = 2 C_n / (nc cbar_n); dir = -1:
 // x = cbar a, f_j = C_j.  tw_g: exp(-i pi m / nc), m < 2 nc (or NULL).
 template <typename T, int NC, class Src>
-__global__ void __launch_bounds__(CTile<Plan<NC>>::L * CTile<Plan<NC>>::TT) k_dct_half(Src src, cpx<T>* __restrict__ out, long long nlines, int nfield,
-                                                  int both, int dir, long long fstride,
-                                                  const cpx<T>* __restrict__ tw_g, cpx<double>* __restrict__ out64,
-                                                  int kz) {
+__global__ void __launch_bounds__(CTile<Plan<NC>>::L * CTile<Plan<NC>>::TT)
+k_dct_half(Src src, cpx<T>* __restrict__ out, long long nlines, int nfield, int both, int dir, long long fstride,
+           const cpx<T>* __restrict__ tw_g, cpx<double>* __restrict__ out64, int kz) {
   using P = Plan<NC>;
   using G = CTile<P>;
   constexpr int E = G::E, L = G::L, LP = L + 1, TT = G::TT;

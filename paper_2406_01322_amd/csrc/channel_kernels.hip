@@ -28,6 +28,18 @@ namespace psms {
 
 namespace {
 
+// The transforms' plans: radix 8 for lines of 128 and 256, half the threads and one
+// exchange (with its barrier) fewer (256 x 256 x 257 in FP64: products 206 -> 185 us,
+// fields 140 -> 128; five steps of 256 x 128 x 129 in MIXED 1433 -> 1424 us).
+template <int N>
+struct DctPlanSel {
+  using type = Plan<N>;
+};
+template <> struct DctPlanSel<128> { using type = PlanT<128, 8, 8, 8, 2>; };
+template <> struct DctPlanSel<256> { using type = PlanT<256, 8, 8, 8, 4>; };
+template <int N>
+using DctPlan = typename DctPlanSel<N>::type;
+
 // 16 lines per workgroup (8 for the 512-point extension, nc = 256): the lanes
 // of a position read 16 consecutive lines (128 bytes in FP32), and the LDS
 // tile stays within 160 KB in FP64.
@@ -192,8 +204,8 @@ __device__ __forceinline__ void with_pair(int q, F&& f) {
 // positions need x_j twice), and a pair's inputs for both its sides.  The step's
 // transforms are bound by these reads and their writes: at 256 x 256 x 257 in FP64
 // the products' took 350 us and the fields' 211 with a workgroup a field reading
-// each input twice, 206 and 150 so (0.52 and 0.24 GB); at 256 x 128 x 129 in FP32
-// 54 and 48 us, now 34 and 33.
+// each input twice, 185 and 128 now (0.52 and 0.24 GB); at 256 x 128 x 129 in FP32
+// 54 and 48 us, now 32 and 32.
 // put(j, a, b) with the sides' inputs a[0], b[0] at j = 0 .. NC, a thread's rows
 // being t, t + TT, ..; PAIRED: j = 0 .. NC / 2, and a[1], b[1] at NC - j.
 template <typename T, class Src, int NC, int TT, bool PAIRED, class Put>
@@ -235,10 +247,10 @@ __device__ __forceinline__ void dct_stage(const Src& src, int q, int t, long lon
 // both: a workgroup transforms both sides of a pair, one after the other; else
 // each side has a workgroup (blockIdx.y = 2 pair + side).
 template <typename T, int N, class Src>
-__global__ void __launch_bounds__(CTile<Plan<N>>::L * CTile<Plan<N>>::TT)
+__global__ void __launch_bounds__(CTile<DctPlan<N>>::L * CTile<DctPlan<N>>::TT)
 k_dct(Src src, cpx<T>* __restrict__ out, long long nlines, int nfield, int both, int dir, long long fstride,
       const cpx<T>* __restrict__ tw_g, cpx<double>* __restrict__ out64, int kz) {
-  using P = Plan<N>;
+  using P = DctPlan<N>;
   using G = CTile<P>;
   constexpr int E = G::E, L = G::L, LP = L + 1, TT = G::TT, NC = N / 2;
   constexpr int RI = first_radix<P, -1>(), RO = last_radix<P, -1>();
@@ -328,10 +340,10 @@ k_dct(Src src, cpx<T>* __restrict__ out, long long nlines, int nfield, int both,
 // starting value.  dir = +1: x = f, a_n = 2 C_n / (nc cbar_n); dir = -1:
 // x = cbar a, f_j = C_j.  tw_g: exp(-i pi m / nc), m < 2 nc (or NULL).
 template <typename T, int NC, class Src>
-__global__ void __launch_bounds__(CTile<Plan<NC>>::L * CTile<Plan<NC>>::TT)
+__global__ void __launch_bounds__(CTile<DctPlan<NC>>::L * CTile<DctPlan<NC>>::TT)
 k_dct_half(Src src, cpx<T>* __restrict__ out, long long nlines, int nfield, int both, int dir, long long fstride,
            const cpx<T>* __restrict__ tw_g, cpx<double>* __restrict__ out64, int kz) {
-  using P = Plan<NC>;
+  using P = DctPlan<NC>;
   using G = CTile<P>;
   constexpr int E = G::E, L = G::L, LP = L + 1, TT = G::TT;
   constexpr int RI = first_radix<P, -1>(), RO = last_radix<P, -1>();
@@ -813,12 +825,12 @@ hipError_t dct_n(const Src& in, cpx<T>* out, long long nlines, int dir, long lon
   // is formed by itself.
   int both = 0;
   if constexpr (N >= 192 && sizeof(T) == 8) {   // nc = N / 2 >= 96
-    using G = CTile<Plan<N / 2>>;
+    using G = CTile<DctPlan<N / 2>>;
     const dim3 grid = dct_grid<Src>((nlines + G::L - 1) / G::L, nfield, both);
     k_dct_half<T, N / 2, Src><<<grid, unsigned(G::L * G::TT), 0, st>>>(in, out, nlines, nfield, both, dir, fstride, tw,
                                                                        out64, kz);
   } else {
-    using G = CTile<Plan<N>>;
+    using G = CTile<DctPlan<N>>;
     const dim3 grid = dct_grid<Src>((nlines + G::L - 1) / G::L, nfield, both);
     k_dct<T, N, Src><<<grid, unsigned(G::L * G::TT), 0, st>>>(in, out, nlines, nfield, both, dir, fstride, tw, out64,
                                                               kz);

@@ -1632,7 +1632,6 @@ struct psms_channel {
   double a_fac, b_fac;
   int nstep;
   int have_state;
-  int d_valid;   // D w, D phi of the current state are in the workspace (the step leaves them)
   template <typename X>
   X* at(size_t off) const {
     return reinterpret_cast<X*>(ws + off);
@@ -1731,14 +1730,15 @@ hipError_t chan_inverse(psms_channel* c, const cpx<T>* band, T* phys, int nf) {
   return psms::launch_rows<T>(g.nx, +1, B, phys, chan_tw<T>(c, true), ra, nf, c->stream);
 }
 
-// D w and D phi of the state, which the fields of a step are formed from
+// D w and D phi of the state, which the fields of a step are formed from.  They are
+// part of the state: init_state and set_state form them on the stream as the step
+// does, so a step that a caller has captured finds those of whatever state was set
+// before its replay (a flag on the host would be read at the capture).
 hipError_t chan_derivatives(psms_channel* c) {
   const psms::ChanGeom& g = c->g;
   cpx<double>* w = c->at<cpx<double>>(c->lay.state) + g.NZL;
-  const hipError_t e = psms::launch_tau_deriv(w, w + g.NZL, c->at<cpx<double>>(c->lay.dw),
-                                              c->at<cpx<double>>(c->lay.dphi), g.sp ? 1 : 2, g.nc, g.NL, c->stream);
-  if (e == hipSuccess) c->d_valid = 1;
-  return e;
+  return psms::launch_tau_deriv(w, w + g.NZL, c->at<cpx<double>>(c->lay.dw), c->at<cpx<double>>(c->lay.dphi),
+                                g.sp ? 1 : 2, g.nc, g.NL, c->stream);
 }
 
 // One step from a state whose D w, D phi are in the workspace; it leaves those
@@ -1858,7 +1858,6 @@ int psms_channel_create(psms_channel** out, const psms_channel_params* p, void* 
   c->coef.forcing = p->forcing;
   c->nstep = 0;
   c->have_state = 0;
-  c->d_valid = 0;
   // line wavenumbers (kx = 2 pi m / lx, ky = 2 pi m / ly over the band) and twiddles
   const psms::ChanGeom& g = c->g;
   std::vector<double> hkx(g.NL), hky(g.NL);
@@ -1941,11 +1940,11 @@ int psms_channel_init_state(psms_channel* c, const double* d_u, const double* d_
     e = hipMemsetAsync(c->ws + L.hist, 0, size_t(3 * g.NZL) * sizeof(cpx<double>), c->stream);
   if (e == hipSuccess)
     e = hipMemsetAsync(c->ws + L.hmean, 0, size_t(2 * (g.nc + 1)) * sizeof(cpx<double>), c->stream);
+  if (e == hipSuccess) e = chan_derivatives(c);
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
   if (e != hipSuccess) return hip_fail(e, "channel_init_state");
   c->nstep = 0;
   c->have_state = 1;
-  c->d_valid = 0;
   // a non-finite input value reaches every coefficient of its line through the
   // transforms: the diagnostics' count finds it
   psms_diag d;
@@ -1975,12 +1974,11 @@ int psms_channel_diagnostics(psms_channel* c, psms_diag* h_out) {
   double* out = part2 + 4 * kChanDiagBlocks;
   const int nb1 = int(std::min<long long>(kChanDiagBlocks, (g.NL + 3) / 4));
   const int nb2 = int(std::min<long long>(kChanDiagBlocks, (g.P + 255) / 256));
-  // D w and D phi, the per-line sums, then u, v, w in FP64 on the collocation grid for the CFL
+  // the per-line sums, then u, v, w in FP64 on the collocation grid for the CFL
   // number (through the step's transform buffers, which hold 4 FP64 fields in
   // MIXED)
-  hipError_t e = c->d_valid ? hipSuccess : chan_derivatives(c);
-  if (e == hipSuccess)
-    e = psms::launch_ch_diag_lines(g, om, w, phi, C64(L.dw), C64(L.dphi), C64(L.mean), kx, ky, part, nb1, st);
+  hipError_t e =
+      psms::launch_ch_diag_lines(g, om, w, phi, C64(L.dw), C64(L.dphi), C64(L.mean), kx, ky, part, nb1, st);
   if (e == hipSuccess)
     e = psms::launch_ch_uvw(g, om, w, C64(L.dw), C64(L.mean), kx, ky, C64(L.R), st);
   if (e == hipSuccess) e = chan_inverse<double>(c, C64(L.R), c->at<double>(L.C), 3);
@@ -2033,10 +2031,10 @@ int psms_channel_set_state(psms_channel* c, const double* d_state, const double*
       e = hipMemsetAsync(c->ws + L.hist + size_t(2 * g.NZL) * sizeof(cpx<double>), 0,
                          size_t(g.NZL) * sizeof(cpx<double>), c->stream);
   }
+  if (e == hipSuccess) e = chan_derivatives(c);
   if (e != hipSuccess) return hip_fail(e, "channel_set_state");
   c->nstep = nstep;
   c->have_state = 1;
-  c->d_valid = 0;
   return PSMS_OK;
 }
 
@@ -2045,10 +2043,6 @@ int psms_channel_step(psms_channel* c, int32_t nsteps) {
   if (nsteps < 0) return fail(PSMS_E_INVAL, "nsteps must be >= 0");
   if (!c->have_state) return fail(PSMS_E_STATE, "step before init_state / set_state");
   const bool mixed = c->p.precision == PSMS_MIXED;
-  if (nsteps > 0 && !c->d_valid) {
-    const hipError_t e = chan_derivatives(c);
-    if (e != hipSuccess) return hip_fail(e, "channel_step");
-  }
   for (int i = 0; i < nsteps; ++i) {
     // after the Adams-Bashforth 1 step every step is the same launch sequence
     // with the same arguments: capture it once and replay it
@@ -2069,10 +2063,7 @@ int psms_channel_step(psms_channel* c, int32_t nsteps) {
     } else {
       e = mixed ? chan_step_once<float>(c) : chan_step_once<double>(c);
     }
-    if (e != hipSuccess) {
-      c->d_valid = 0;
-      return hip_fail(e, "channel_step");
-    }
+    if (e != hipSuccess) return hip_fail(e, "channel_step");
     ++c->nstep;
   }
   return PSMS_OK;

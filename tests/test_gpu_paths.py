@@ -290,3 +290,35 @@ def test_adjoint_x_stage(n):
     assert abs(J - J0) <= 1e-10 * abs(J0)
     assert np.linalg.norm(_host(d) - d0) <= 1e-10 * np.linalg.norm(d0)
     assert abs(w - w0) <= 1e-10 * abs(w0)
+
+
+# A step that the caller has captured in its own graph, replayed after other states
+# were set: what the same step gives when it is launched directly, bit for bit.
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("single", [False, True])
+def test_captured_channel_step_follows_the_state(precision, single):
+    from paper_2406_01322_amd.psms import Channel
+    with torch.cuda.stream(torch.cuda.Stream()):
+        stream = torch.cuda.current_stream()
+        c, d = (Channel(16, 12, 16, 20.0, 1.0, 0.2, 5.0, 1e-3, precision=precision, single_phase=single, stream=stream)
+                for _ in range(2))
+        states = []
+        for seed in (1, 2, 3):
+            f = _channel_fields(16, 12, 16, seed)
+            d.init_state(*[_dev(x) for x in (f[:3] + (np.zeros_like(f[3]),) if single else f)])
+            d.step(2)
+            states.append([t.clone() for t in d.get_state(with_history=True)])
+        c.set_state(*states[0], nstep=2)
+        c.step(1)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            c.step(1)
+        for s in (1, 2, 0, 1):
+            c.set_state(*states[s], nstep=2)
+            graph.replay()
+            d.set_state(*states[s], nstep=2)
+            d.step(1)
+            torch.cuda.synchronize()
+            assert all(torch.equal(x, y) for x, y in zip(c.get_state(), d.get_state())), s
+        torch.cuda.synchronize()

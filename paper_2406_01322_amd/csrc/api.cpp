@@ -950,11 +950,39 @@ int psms_wall_solve(const psms_wall_args* a, void* d_work, size_t bytes, void* s
   hipError_t e;
 #define PSMS_TRY(x) \
   if ((e = (x)) != hipSuccess) return hip_fail(e, "wall_solve")
+  const size_t arr = size_t(nc + 1) * size_t(nl) * sizeof(cpx<double>);
+  auto overlap = [&](const double* p, const double* q) {
+    const uintptr_t x = reinterpret_cast<uintptr_t>(p), y = reinterpret_cast<uintptr_t>(q);
+    return x < y + arr && y < x + arr;
+  };
+  // p, or a copy of it in the workspace if it is `shared` with an output of the launch that reads it
+  auto source = [&](const double* p, bool shared, size_t slot, const cpx<double>** out) {
+    *out = shared ? C(slot) : CC(p);
+    return shared ? hipMemcpyAsync(C(slot), p, arr, hipMemcpyDeviceToDevice, st) : hipSuccess;
+  };
+  // u and v may take the place of w or omega
+  auto uv = [&]() {
+    const cpx<double>*om, *wv;
+    hipError_t r = source(a->d_om, overlap(a->d_u, a->d_om) || overlap(a->d_v, a->d_om), L.psi, &om);
+    if (r == hipSuccess) r = source(a->d_w, overlap(a->d_u, a->d_w) || overlap(a->d_v, a->d_w), L.wt, &wv);
+    if (r == hipSuccess) r = psms::launch_cheb_uv(om, wv, CM(a->d_u), CM(a->d_v), nc, nl, a->d_kx, a->d_ky, st);
+    return r;
+  };
   if (psms::tau_pieces_nc(nc)) {
-    const psms::WallTauArgs t{CC(a->d_g_om), CC(a->d_g_w), CC(a->d_g_phi), CM(a->d_om), CM(a->d_w), CM(a->d_phi),
+    // one launch for the three equations: each may be solved in the place of its own
+    // right-hand side, and one in the place of another's through a copy
+    const double *const g[3] = {a->d_g_om, a->d_g_w, a->d_g_phi}, *const f[3] = {a->d_om, a->d_w, a->d_phi};
+    const size_t slot[3] = {L.psi, L.wt, L.psit};
+    const cpx<double>* src[3];
+    for (int i = 0; i < 3; ++i) {
+      bool shared = false;
+      for (int j = 0; j < 3; ++j) shared = shared || (overlap(g[i], f[j]) && !(i == j && g[i] == f[j]));
+      PSMS_TRY(source(g[i], shared, slot[i], &src[i]));
+    }
+    const psms::WallTauArgs t{src[0], src[1], src[2], CM(a->d_om), CM(a->d_w), CM(a->d_phi),
                               a->d_kx, a->d_ky, nl, a->beta_ns, a->beta_a, a->beta_b};
     PSMS_TRY(psms::launch_wall_tau(t, nc, st));
-    PSMS_TRY(psms::launch_cheb_uv(CC(a->d_om), CC(a->d_w), CM(a->d_u), CM(a->d_v), nc, nl, a->d_kx, a->d_ky, st));
+    PSMS_TRY(uv());
     return PSMS_OK;
   }
   // chain lengths outside the pieced solves: one lane per chain
@@ -979,7 +1007,7 @@ int psms_wall_solve(const psms_wall_args* a, void* d_work, size_t bytes, void* s
   b.p[0] = psms::HelmProblem{C(L.xi), CM(a->d_phi), xw, nl, a->beta_b, a->d_kx, a->d_ky, 1, z0, z0};
   PSMS_TRY(psms::launch_helm_batch(b, nc, st));
   PSMS_TRY(psms::launch_influence(CM(a->d_w), C(L.wt), C(L.wb), nc, nl, a->d_kx, a->d_ky, st));
-  PSMS_TRY(psms::launch_cheb_uv(CC(a->d_om), CC(a->d_w), CM(a->d_u), CM(a->d_v), nc, nl, a->d_kx, a->d_ky, st));
+  PSMS_TRY(uv());
 #undef PSMS_TRY
   return PSMS_OK;
 }

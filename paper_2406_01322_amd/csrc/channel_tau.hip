@@ -31,7 +31,8 @@ constexpr int kTauPieces = 8;
 constexpr int tau_len(int nc) { return (nc / 2 + 1 + kTauPieces - 1) / kTauPieces; }
 
 // The rows (tau_rows.hpp) of chain length NC at every piece's slots, by parity:
-// c_{n-2} q1, e_n q2, e_{n+2} q3, zero for n < 2 and past the chain.  There the map
+// c_{n-2} q1, e_n q2, e_{n+2} q3, zero for n < 2 and past the chain (there e_n q2 is 1:
+// a row of the others' size, since they are scaled by beta).  There the map
 // is X = Y = 0 whatever comes in, which is right above the chain and unread below
 // it, so the sweeps need no branch.  A wavefront reads LEN consecutive entries of
 // each at uniform addresses: a few wide scalar loads that are waited for once (a
@@ -47,7 +48,10 @@ constexpr TauTab<NC> make_tau_tab() {
   for (int p = 0; p < 2; ++p)
     for (int i = 1; i < kTauPieces * tau_len(NC); ++i) {
       const int n = p + 2 * i;
-      if (n > NC) break;
+      if (n > NC) {
+        t.b[p][i] = 1.0;
+        continue;
+      }
       t.a[p][i] = (n == 2 ? 2.0 : 1.0) * q.q[0][n];
       t.b[p][i] = n <= NC - 2 ? q.q[1][n] : 0.0;
       t.c[p][i] = n + 2 <= NC - 2 ? q.q[2][n] : 0.0;
@@ -133,13 +137,16 @@ __device__ __forceinline__ void tau_reduce(const W& t, double be, double (&r)[W:
     gn[c] = t.pc + 1 < PC ? t.get(c, t.pc + 1) : 0.0;
   }
   __syncthreads();
-  // right-hand sides R and the piece's map (x, d, y) -> (xx x + xd d, dx x + dd d, al y + u x + v d)
-  double xx = 1.0, xd = 0.0, dx = 0.0, dd = 1.0, al = 1.0, u[NR], v[NR];
+  // right-hand sides R and the piece's map (x, d, y) -> (xx x + xd d, dx x + dd d, al y + u x + v d).
+  // The rows are taken times sc, a power of two near 1 / (1 + be), which leaves the
+  // map's entries over dd as they are and keeps a piece's product in range for any be
+  const double sc = ldexp(1.0, -__builtin_amdgcn_frexp_exp(1.0 + be)), bes = be * sc;
+  double xx = 1.0, xd = 0.0, dx = 0.0, dd = 1.0, al = 1.0, u[NR], v[NR];   // u, v before their factor sc
 #pragma unroll
   for (int c = 0; c < NR; ++c) u[c] = v[c] = 0.0;
 #pragma unroll
   for (int k = LEN - 1; k >= 0; --k) {
-    const double A = be * ra[k], B = -(1.0 + be * rb[k]), C = be * rc[k];
+    const double A = bes * ra[k], B = -(sc + bes * rb[k]), C = bes * rc[k];
 #pragma unroll
     for (int c = 0; c < NR; ++c) {
       const double g0 = r[k][c], gm = k > 0 ? r[k > 0 ? k - 1 : 0][c] : gp[c];
@@ -155,26 +162,17 @@ __device__ __forceinline__ void tau_reduce(const W& t, double be, double (&r)[W:
     dx = ndx;
     dd = ndd;
     al = -C * al;
-    if (LEN > 9 && k % 8 == 0 && k > 0) {   // keep the map's entries in range: divide by 2^exponent(dd)
-      const int ex = -__builtin_amdgcn_frexp_exp(dd);
-      xx = ldexp(xx, ex); xd = ldexp(xd, ex); dx = ldexp(dx, ex); dd = ldexp(dd, ex); al = ldexp(al, ex);
-#pragma unroll
-      for (int c = 0; c < NR; ++c) {
-        u[c] = ldexp(u[c], ex);
-        v[c] = ldexp(v[c], ex);
-      }
-    }
   }
   {
-    const double inv = 1.0 / dd;
+    const double inv = 1.0 / dd, invs = inv * sc;
     t.put(0, xx * inv);
     t.put(1, xd * inv);
     t.put(2, dx * inv);
     t.put(3, al * inv);
 #pragma unroll
     for (int c = 0; c < NR; ++c) {
-      t.put(4 + c, u[c] * inv);
-      t.put(4 + NR + c, v[c] * inv);
+      t.put(4 + c, u[c] * invs);
+      t.put(4 + NR + c, v[c] * invs);
     }
   }
   __syncthreads();

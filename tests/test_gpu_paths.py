@@ -355,3 +355,25 @@ def test_wall_solve_in_place(nc, nl, place):
     for k, name in (("om", "omega"), ("w", "w"), ("phi", "phi"), ("u", "u"), ("v", "v")):
         if k not in over.values():
             assert torch.equal(at[k], want[name]), k
+
+
+# beta far beyond any time step's, where the product of a piece's rows passes the
+# largest double: w and phi as the dense oracle has them, to the bar of the other
+# wall-solve tests.  (Not omega: its last coefficients are differences of terms of beta
+# times their size, here and in the oracle.)
+@pytest.mark.parametrize("nc", [16, 32, 64, 96, 128, 256])
+@pytest.mark.parametrize("beta", [1e38, 1e60, 1e150])
+def test_wall_solve_of_very_large_beta(nc, beta):
+    from oracle import channel as ch
+    from paper_2406_01322_amd import psms
+    rng = np.random.default_rng(nc)
+    kx, ky = np.array([0.0, 0.5, 3.0]), np.array([0.0, -1.0, 2.0])
+    g = [(rng.standard_normal((nc + 1, 3)) + 1j * rng.standard_normal((nc + 1, 3)))
+         * np.exp(-0.05 * np.arange(nc + 1))[:, None] for _ in range(3)]
+    k2 = kx ** 2 + ky ** 2
+    want = ch.wall_normal_solve_lines(*g, kx, ky, k2 + beta, k2 + beta, k2 + 700.0)
+    got = psms.wall_solve(_dev(kx), _dev(ky), beta, beta, 700.0, *[_dev(x) for x in g])
+    assert all(np.all(np.isfinite(_host(x))) for x in got.values())
+    for key in ("w", "phi"):
+        a, b = _host(got[key]), want[key]
+        assert np.all(np.max(np.abs(a - b), axis=0) <= 1e-11 * np.max(np.abs(b), axis=0)), key

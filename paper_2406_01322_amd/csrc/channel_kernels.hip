@@ -625,7 +625,9 @@ __global__ void __launch_bounds__(256) k_cheb_uv(const cpx<double>* __restrict__
 // per line of scratch.
 
 // downward sweep of parity p: a_i = X_i a_{i-1} + Y_i for the indices
-// n = p + 2 i, i = m..1 (X in xw, Y in f)
+// n = p + 2 i, i = m..1 (X in xw, Y in f).  TAB: nc <= kTauQMax, the rows' constants
+// from the table; else by division.
+template <bool TAB>
 __device__ __forceinline__ void helm_down(const cpx<double>* __restrict__ g, cpx<double>* __restrict__ f,
                                           double* __restrict__ xw, int nc, long long nlines, double be, int p,
                                           long long l) {
@@ -643,7 +645,10 @@ __device__ __forceinline__ void helm_down(const cpx<double>* __restrict__ g, cpx
     const double cm2 = (n - 2 == 0) ? 2.0 : 1.0;
     const double en = (n <= nc - 2) ? 1.0 : 0.0;
     const double en2 = (n + 2 <= nc - 2) ? 1.0 : 0.0;
-    const double q1 = kTauQ.q[0][n], q2 = kTauQ.q[1][n], q3 = kTauQ.q[2][n];
+    const double dn = double(n);
+    const double q1 = TAB ? kTauQ.q[0][n] : 1.0 / (4.0 * dn * (dn - 1.0));
+    const double q2 = TAB ? kTauQ.q[1][n] : 1.0 / (2.0 * (dn * dn - 1.0));
+    const double q3 = TAB ? kTauQ.q[2][n] : 1.0 / (4.0 * dn * (dn + 1.0));
     const double A = cm2 * be * q1;
     const double B = -(1.0 + en * be * q2);
     const double C = en2 * be * q3;
@@ -703,6 +708,7 @@ __device__ __forceinline__ void helm_up2(cpx<double>* __restrict__ f, const doub
   }
 }
 
+template <bool TAB>
 __device__ __forceinline__ void helm_line(const cpx<double>* __restrict__ g, cpx<double>* __restrict__ f,
                                           double* __restrict__ xw, int nc, long long nlines,
                                           const double* __restrict__ beta_line, double beta_add,
@@ -722,31 +728,33 @@ __device__ __forceinline__ void helm_line(const cpx<double>* __restrict__ g, cpx
   const bool plus = (p == 0) != neu;          // Dirichlet even, Neumann odd: (top + bottom) / 2
   const cpx<double> s = plus ? cpx<double>{0.5 * (top.re + bot.re), 0.5 * (top.im + bot.im)}
                              : cpx<double>{0.5 * (top.re - bot.re), 0.5 * (top.im - bot.im)};
-  helm_down(g, f, xw, nc, nlines, be, p, l);
+  helm_down<TAB>(g, f, xw, nc, nlines, be, p, l);
   double SP;
   cpx<double> SQ;
   helm_up1(f, xw, nc, nlines, p, l, neu, SP, SQ);
   helm_up2(f, xw, nc, nlines, p, l, cpx<double>{(s.re - SQ.re) / SP, (s.im - SQ.im) / SP});
 }
 
+template <bool TAB>
 __global__ void k_helm(const cpx<double>* __restrict__ g, cpx<double>* __restrict__ f, double* __restrict__ xw,
                        int nc, long long nlines, const double* __restrict__ beta_line, double beta_add,
                        const double* __restrict__ kx, const double* __restrict__ ky, int neumann,
                        const cpx<double>* __restrict__ bcv, cpx<double> top_c, cpx<double> bot_c) {
   const long long id = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (id >= 2 * nlines) return;
-  helm_line(g, f, xw, nc, nlines, beta_line, beta_add, kx, ky, neumann != 0, bcv, top_c, bot_c, id);
+  helm_line<TAB>(g, f, xw, nc, nlines, beta_line, beta_add, kx, ky, neumann != 0, bcv, top_c, bot_c, id);
 }
 
 // Several independent problems in one launch (blockIdx.y selects the problem):
 // each thread's elimination is a sequential chain, so more chains per launch
 // hide more of their memory latency.
+template <bool TAB>
 __global__ void k_helm_batch(HelmBatch b, int nc) {
   const HelmProblem& P = b.p[blockIdx.y];
   const long long id = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (id >= 2 * P.nlines) return;
-  helm_line(P.g, P.f, P.xw, nc, P.nlines, nullptr, P.beta_add, P.kx, P.ky, P.neumann != 0, nullptr, P.top_c, P.bot_c,
-            id);
+  helm_line<TAB>(P.g, P.f, P.xw, nc, P.nlines, nullptr, P.beta_add, P.kx, P.ky, P.neumann != 0, nullptr, P.top_c,
+                 P.bot_c, id);
 }
 
 // w = w_p + c_t w_t + c_b w_b with (c_t, c_b) making w'(+1) = w'(-1) = 0;
@@ -918,8 +926,11 @@ hipError_t launch_chebd(const cpx<double>* a, cpx<double>* d, int nc, long long 
 hipError_t launch_helm(const cpx<double>* g, cpx<double>* f, double* xw, int nc, long long nlines,
                        const double* beta_line, double beta_add, const double* kx, const double* ky, int neumann,
                        const cpx<double>* bcv, cpx<double> top_c, cpx<double> bot_c, hipStream_t st) {
-  k_helm<<<blocks(2 * nlines, 64), 64, 0, st>>>(g, f, xw, nc, nlines, beta_line, beta_add, kx, ky, neumann, bcv,
-                                                   top_c, bot_c);
+  const unsigned nb = blocks(2 * nlines, 64);
+  if (nc <= kTauQMax)
+    k_helm<true><<<nb, 64, 0, st>>>(g, f, xw, nc, nlines, beta_line, beta_add, kx, ky, neumann, bcv, top_c, bot_c);
+  else
+    k_helm<false><<<nb, 64, 0, st>>>(g, f, xw, nc, nlines, beta_line, beta_add, kx, ky, neumann, bcv, top_c, bot_c);
   return hipGetLastError();
 }
 
@@ -931,7 +942,9 @@ hipError_t launch_helm_batch(const HelmBatch& b, int nc, hipStream_t st) {
     most = most > b.p[i].nlines ? most : b.p[i].nlines;
   }
   if (b.np == 0 || most == 0) return hipSuccess;
-  k_helm_batch<<<dim3(blocks(2 * most, 64), unsigned(b.np)), 64, 0, st>>>(b, nc);
+  const dim3 grid(blocks(2 * most, 64), unsigned(b.np));
+  if (nc <= kTauQMax) k_helm_batch<true><<<grid, 64, 0, st>>>(b, nc);
+  else k_helm_batch<false><<<grid, 64, 0, st>>>(b, nc);
   return hipGetLastError();
 }
 

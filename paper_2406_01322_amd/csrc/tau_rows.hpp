@@ -10,7 +10,7 @@
 
 namespace psms {
 
-constexpr int kTauQMax = 256;   // largest nc of the tau solves
+constexpr int kTauQMax = 256;   // largest n of the table
 
 // The coefficients of the tau rows that depend only on the index n:
 // q1 = 1 / (4 n (n - 1)), q2 = 1 / (2 (n^2 - 1)), q3 = 1 / (4 n (n + 1)), n >= 2,

@@ -377,3 +377,26 @@ def test_wall_solve_of_very_large_beta(nc, beta):
     for key in ("w", "phi"):
         a, b = _host(got[key]), want[key]
         assert np.all(np.max(np.abs(a - b), axis=0) <= 1e-11 * np.max(np.abs(b), axis=0)), key
+
+
+# Chains longer than the table of the rows' constants (n <= 256), to the bars that the
+# shorter ones are held to.
+@pytest.mark.parametrize("kind", ["dirichlet", "neumann"])
+@pytest.mark.parametrize("nc", [257, 258, 300, 513])
+def test_helmholtz_beyond_the_table(kind, nc):
+    from oracle import channel as ch
+    from paper_2406_01322_amd import psms
+    rng = np.random.default_rng(nc)
+    g = (rng.standard_normal((nc + 1, 5)) + 1j * rng.standard_normal((nc + 1, 5))) \
+        * np.exp(-0.03 * np.arange(nc + 1))[:, None]
+    beta = 1e3 * (0.5 + rng.random(5))
+    bcv = rng.standard_normal((5, 2)) + 1j * rng.standard_normal((5, 2))
+    want = np.stack([ch.helmholtz(g[:, l], beta[l], kind, *bcv[l]) for l in range(5)], axis=1)
+    for f in (psms.cheb_helmholtz, psms.cheb_helmholtz_noalloc):
+        got = _host(f(_dev(g), _dev(beta), kind, _dev(bcv)))
+        assert np.max(np.abs(got - want)) <= 1e-11 * np.max(np.abs(want))
+
+
+@pytest.mark.parametrize("nc,nl", [(258, 7), (287, 3)])
+def test_wall_solve_beyond_the_table(nc, nl):
+    test_pieced_wall_solve_sizes(nc, nl)

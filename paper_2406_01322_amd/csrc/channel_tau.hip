@@ -464,15 +464,17 @@ __device__ __forceinline__ void d2_carry(const W& t, int v, double (&a)[2], doub
   }
 }
 
-// D of the piece's solution r into out (indices n - 1; out_nc = 0)
+// D of the piece's solution r into out (indices n - 1; out_nc = 0).  The sums are
+// explicit fused multiply-adds: the step and k_tau_deriv have to give the same bits,
+// and which products the compiler fuses by itself depends on the kernel around them.
 template <class W>
 __device__ __forceinline__ void d_store(const W& t, cpx<double>* __restrict__ out, long long nl, unsigned l, bool valid,
                                         const double (&r)[W::LEN][2]) {
   double a[2] = {0.0, 0.0}, c[2], n = t.dn(0);
 #pragma unroll
   for (int k = 0; k < W::LEN; ++k, n += 2.0) {   // r = 0 past the chain
-    a[0] += n * r[k][0];
-    a[1] += n * r[k][1];
+    a[0] = __builtin_fma(n, r[k][0], a[0]);
+    a[1] = __builtin_fma(n, r[k][1], a[1]);
   }
   t.put(0, 2.0 * a[0]);
   t.put(1, 2.0 * a[1]);
@@ -482,8 +484,8 @@ __device__ __forceinline__ void d_store(const W& t, cpx<double>* __restrict__ ou
   double tn = 2.0 * t.dn(W::LEN - 1);
 #pragma unroll
   for (int k = W::LEN - 1; k >= 0; --k, tn -= 4.0) {
-    c[0] += tn * r[k][0];
-    c[1] += tn * r[k][1];
+    c[0] = __builtin_fma(tn, r[k][0], c[0]);
+    c[1] = __builtin_fma(tn, r[k][1], c[1]);
     if (t.in(k) && t.n(k) >= 1) {
       const double s = t.n(k) == 1 ? 0.5 : 1.0;
       (out + (long long)(t.n(k) - 1) * nl)[l] = cpx<double>{s * c[0], s * c[1]};

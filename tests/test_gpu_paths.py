@@ -400,3 +400,26 @@ def test_helmholtz_beyond_the_table(kind, nc):
 @pytest.mark.parametrize("nc,nl", [(258, 7), (287, 3)])
 def test_wall_solve_beyond_the_table(nc, nl):
     test_pieced_wall_solve_sizes(nc, nl)
+
+
+# A run continued from a saved state takes the bits of the run that saved it: the
+# derivatives of a state that is set are those that the step leaves, in every form of
+# the step's kernel (longest chains, both parities in a workgroup, single phase).
+@pytest.mark.parametrize("nc,walls,single", [(8, "nn", False), (48, "fn", False), (96, "nf", False), (128, "nn", False),
+                                             (128, "fn", False), (128, "ff", False), (256, "nn", False),
+                                             (256, "fn", False), (256, "nn", True)])
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_restart_takes_the_same_bits(nc, walls, single, precision):
+    from paper_2406_01322_amd.psms import Channel
+    kinds = tuple({"n": "noslip", "f": "freeslip"}[c] for c in walls)
+    a, b = (Channel(24, 16, nc, 150.0, 3.0, 0.1, 10.0, 1e-4, walls=kinds, single_phase=single, precision=precision)
+            for _ in range(2))
+    f = list(_channel_fields(24, 16, nc, nc))
+    if single:
+        f[3] = np.zeros_like(f[3])
+    a.init_state(*[_dev(x) for x in f])
+    a.step(2)
+    b.set_state(*[t.clone() for t in a.get_state(with_history=True)], nstep=2)
+    for s in (a, b):
+        s.step(2)
+    assert all(torch.equal(x, y) for x, y in zip(a.get_state(with_history=True), b.get_state(with_history=True)))

@@ -27,8 +27,17 @@ namespace psms {
 
 namespace {
 
-constexpr int kTauPieces = 8;
-constexpr int tau_len(int nc) { return (nc / 2 + 1 + kTauPieces - 1) / kTauPieces; }
+// Pieces of a chain: the smallest power of two with at most 7 terms a piece, up to 8.
+// More leave wavefronts without terms, which costs nothing while a launch is a few
+// workgroups and everything once it fills the chip (60000 lines: nc = 4 22 us where 8
+// pieces took 101, nc = 16 43 against 123; 15000 lines, nc = 48 37 against 55; 256 x
+// 128 x 49 channel step, FP64 161 against 170).
+constexpr int tau_pieces(int nc) {
+  int p = 1;
+  while (p < 8 && nc / 2 + 1 > 7 * p) p *= 2;
+  return p;
+}
+constexpr int tau_len(int nc) { return (nc / 2 + 1 + tau_pieces(nc) - 1) / tau_pieces(nc); }
 
 // The rows (tau_rows.hpp) of chain length NC at every piece's slots, by parity:
 // c_{n-2} q1, e_n q2, e_{n+2} q3, zero for n < 2 and past the chain (there e_n q2 is 1:
@@ -39,14 +48,15 @@ constexpr int tau_len(int nc) { return (nc / 2 + 1 + kTauPieces - 1) / kTauPiece
 // scalar load for every term, waited for one by one, took a third of the kernel).
 template <int NC>
 struct TauTab {
-  double a[2][kTauPieces * tau_len(NC)], b[2][kTauPieces * tau_len(NC)], c[2][kTauPieces * tau_len(NC)];
+  static constexpr int SLOTS = tau_pieces(NC) * tau_len(NC);
+  double a[2][SLOTS], b[2][SLOTS], c[2][SLOTS];
 };
 template <int NC>
 constexpr TauTab<NC> make_tau_tab() {
   TauTab<NC> t{};
   const TauQ q = make_tau_q();
   for (int p = 0; p < 2; ++p)
-    for (int i = 1; i < kTauPieces * tau_len(NC); ++i) {
+    for (int i = 1; i < TauTab<NC>::SLOTS; ++i) {
       const int n = p + 2 * i;
       if (n > NC) {
         t.b[p][i] = 1.0;
@@ -67,7 +77,7 @@ __constant__ const TauTab<NC> kTauTab = make_tau_tab<NC>();
 // blockIdx.z.
 template <int NC_, int NV_, bool BOTH_ = false>
 struct TauWave {
-  static constexpr int NC = NC_, PC = kTauPieces, NV = NV_;
+  static constexpr int NC = NC_, PC = tau_pieces(NC_), NV = NV_;
   static constexpr bool BOTH = BOTH_;
   static constexpr int NW = BOTH ? 2 * PC : PC;
   static constexpr int LEN = tau_len(NC);
@@ -325,7 +335,7 @@ __device__ __forceinline__ void tau_store(const W& t, cpx<double>* __restrict__ 
 // chain took three launches of 55 us and 174 us for the influence sums.
 // ---------------------------------------------------------------------------
 template <int NC>
-__global__ void __launch_bounds__(512) k_wall_tau(WallTauArgs a) {
+__global__ void __launch_bounds__(64 * tau_pieces(NC)) k_wall_tau(WallTauArgs a) {
   using W = TauWave<NC, 12>;
   __shared__ double sh[W::NV * W::NW * 64];
   const W t(sh);
@@ -540,7 +550,7 @@ __device__ __forceinline__ void chan_a0(const W& t, int bc, const TauSums<2>& S,
 //   U, V   x = T_xz, T_yz of the mean line, f = 0
 // then the right-hand side from the state and one or two solves.
 template <int NC, bool BOTH>
-__global__ void __launch_bounds__(BOTH ? 1024 : 512) k_chan_tau(ChanTauArgs a) {
+__global__ void __launch_bounds__((BOTH ? 128 : 64) * tau_pieces(NC)) k_chan_tau(ChanTauArgs a) {
   using W = TauWave<NC, 9, BOTH>;
   constexpr int LEN = W::LEN;
   __shared__ double sh[W::NV * W::NW * 64];
@@ -715,7 +725,7 @@ __global__ void __launch_bounds__(BOTH ? 1024 : 512) k_chan_tau(ChanTauArgs a) {
 // of the step's own derivatives, so that a run continued from a saved state
 // takes the same bits as the run that saved it.
 template <int NC>
-__global__ void __launch_bounds__(512) k_tau_deriv(const cpx<double>* __restrict__ w, const cpx<double>* __restrict__ phi,
+__global__ void __launch_bounds__(64 * tau_pieces(NC)) k_tau_deriv(const cpx<double>* __restrict__ w, const cpx<double>* __restrict__ phi,
                                                    cpx<double>* __restrict__ dw, cpx<double>* __restrict__ dphi,
                                                    long long nl) {
   using W = TauWave<NC, 2>;
@@ -733,7 +743,7 @@ __global__ void __launch_bounds__(512) k_tau_deriv(const cpx<double>* __restrict
 // at both walls (even parity) or +-1 (odd), w from it, zero at the walls: wh
 // [nc+1][nl], and mh[parity][nl] = sum n^2 wh_n.
 template <int NC>
-__global__ void __launch_bounds__(512) k_tau_hom(double beta, const double* __restrict__ kx,
+__global__ void __launch_bounds__(64 * tau_pieces(NC)) k_tau_hom(double beta, const double* __restrict__ kx,
                                                  const double* __restrict__ ky, long long nl, double* __restrict__ wh,
                                                  double* __restrict__ mh) {
   using W = TauWave<NC, 6>;
@@ -783,8 +793,8 @@ hipError_t launch_chan_tau(const ChanTauArgs& a, int nc, hipStream_t st) {
   switch (nc) {
 #define PSMS_CASE(NC) \
   case NC: \
-    if (both) k_chan_tau<NC, true><<<grid, 1024, 0, st>>>(a); \
-    else k_chan_tau<NC, false><<<grid, 512, 0, st>>>(a); \
+    if (both) k_chan_tau<NC, true><<<grid, 128 * tau_pieces(NC), 0, st>>>(a); \
+    else k_chan_tau<NC, false><<<grid, 64 * tau_pieces(NC), 0, st>>>(a); \
     return hipGetLastError();
     PSMS_FOR_EACH_TAU_NC(PSMS_CASE)
 #undef PSMS_CASE
@@ -797,7 +807,7 @@ hipError_t launch_tau_deriv(const cpx<double>* w, const cpx<double>* phi, cpx<do
   if (nl < 1 || narr < 1 || narr > 2) return hipErrorInvalidValue;
   const dim3 grid(unsigned((nl + 63) / 64), unsigned(narr), 2);
   switch (nc) {
-#define PSMS_CASE(NC) case NC: k_tau_deriv<NC><<<grid, 512, 0, st>>>(w, phi, dw, dphi, nl); return hipGetLastError();
+#define PSMS_CASE(NC) case NC: k_tau_deriv<NC><<<grid, 64 * tau_pieces(NC), 0, st>>>(w, phi, dw, dphi, nl); return hipGetLastError();
     PSMS_FOR_EACH_TAU_NC(PSMS_CASE)
 #undef PSMS_CASE
   }
@@ -810,7 +820,7 @@ hipError_t launch_tau_hom(double beta, const double* kx, const double* ky, int n
   const dim3 grid(unsigned((nl + 63) / 64), 1, 2);
   switch (nc) {
 #define PSMS_CASE(NC) \
-  case NC: k_tau_hom<NC><<<grid, 512, 0, st>>>(beta, kx, ky, nl, wh, mh); return hipGetLastError();
+  case NC: k_tau_hom<NC><<<grid, 64 * tau_pieces(NC), 0, st>>>(beta, kx, ky, nl, wh, mh); return hipGetLastError();
     PSMS_FOR_EACH_TAU_NC(PSMS_CASE)
 #undef PSMS_CASE
   }
@@ -822,7 +832,7 @@ hipError_t launch_wall_tau(const WallTauArgs& a, int nc, hipStream_t st) {
   const dim3 grid(unsigned((a.nl + 63) / 64), 3, 2);
   switch (nc) {
 #define PSMS_CASE(NC) \
-  case NC: k_wall_tau<NC><<<grid, 512, 0, st>>>(a); return hipGetLastError();
+  case NC: k_wall_tau<NC><<<grid, 64 * tau_pieces(NC), 0, st>>>(a); return hipGetLastError();
     PSMS_FOR_EACH_TAU_NC(PSMS_CASE)
 #undef PSMS_CASE
   }

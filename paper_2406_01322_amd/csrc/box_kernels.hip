@@ -585,7 +585,7 @@ k_xfield(const BoxDev* __restrict__ boxes, int box0, const cpx<T>* __restrict__ 
       for (int e = 0; e < E; ++e) {
         cpx<T> ph[NV][1];
 #pragma unroll
-        for (int g = 0; g < NV; ++g) ph[g][0] = lds[g][e * 64 + lane];
+        for (int g = 0; g < NV; ++g) ph[g][0] = g == F ? v[0][e] : lds[g][e * 64 + lane];   // its own is at hand
         v[0][e] = cpx<T>{xproduct<F>(ph, 0, 0, cs), xproduct<F>(ph, 0, 1, cs)};
       }
     }

@@ -435,3 +435,28 @@ def test_wall_solve_piece_counts(nc, nl):
 @pytest.mark.parametrize("nc,walls", [(4, "fn"), (12, "fn"), (16, "nf"), (24, "fn"), (32, "nf")])
 def test_channel_step_piece_counts(nc, walls):
     test_channel_step_sizes_and_walls(24, 16, nc, walls, False)
+
+
+# The longest chains against the oracle on every coefficient: two-phase at 17 slots a
+# piece, and each pair of walls that is not no-slip at both, an AB1 and an AB2 step
+# from the oracle's state.  State to 1e-12 of each field's maximum, the explicit terms
+# to 4e-9 (nc / 256)^2, as for the other one-step tests.
+@pytest.mark.parametrize("nc,walls", [(256, "nn")] + [(nc, w) for nc in (96, 128, 256) for w in ("fn", "nf", "ff")])
+@pytest.mark.parametrize("nprev", [0, 1])
+def test_long_chains_one_step_parity(nc, walls, nprev):
+    from oracle import channel_step as cs
+    from paper_2406_01322_amd.psms import Channel
+    kinds = tuple({"n": "noslip", "f": "freeslip"}[c] for c in walls)
+    prm = cs.ChannelParams(nx=16, ny=12, nc=nc, re=150.0, we=3.0, ch=0.1, pe=10.0, dt=1e-4, walls=kinds)
+    st = cs.run(cs.init_state(*_channel_fields(16, 12, nc, nc), prm), prm, nprev)
+    c = Channel(16, 12, nc, prm.re, prm.we, prm.ch, prm.pe, prm.dt, walls=kinds)
+    c.set_state(*[_dev(x) for x in (np.stack([st["om"], st["w"], st["phi"]]), st["mean"],
+                                    np.stack([st["h_om"], st["h_w"], st["h_phi"]]), st["h_mean"])], nstep=nprev)
+    c.step(1)
+    want = cs.step(st, prm)
+    state, mean, hist, hmean = (_host(x) for x in c.get_state(with_history=True))
+    bar, hbar = 1e-12, 4e-9 * (nc / 256.0) ** 2
+    for a, b, tol in ((state[0], want["om"], bar), (state[1], want["w"], bar), (state[2], want["phi"], bar),
+                      (mean, want["mean"], bar), (hist[0], want["h_om"], hbar), (hist[1], want["h_w"], hbar),
+                      (hist[2], want["h_phi"], hbar), (hmean, want["h_mean"], hbar)):
+        assert np.max(np.abs(a - b)) <= tol * np.max(np.abs(b))

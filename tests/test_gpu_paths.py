@@ -460,3 +460,13 @@ def test_long_chains_one_step_parity(nc, walls, nprev):
                       (mean, want["mean"], bar), (hist[0], want["h_om"], hbar), (hist[1], want["h_w"], hbar),
                       (hist[2], want["h_phi"], hbar), (hmean, want["h_mean"], hbar)):
         assert np.max(np.abs(a - b)) <= tol * np.max(np.abs(b))
+
+
+# The same for the two smallest sizes, with boxes enough (more than 4096 lines of the
+# band) to leave the z stage of few lines.
+@pytest.mark.parametrize("n,boxes", [(8, 274), (12, 147)])
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_z_stages_give_the_same_bits_smallest(n, boxes, precision):
+    K = (n - 1) // 3
+    assert (2 * K + 1) * (K + 1) * boxes > 4096
+    test_z_stages_give_the_same_bits(n, boxes, precision)

@@ -470,3 +470,58 @@ def test_z_stages_give_the_same_bits_smallest(n, boxes, precision):
     K = (n - 1) // 3
     assert (2 * K + 1) * (K + 1) * boxes > 4096
     test_z_stages_give_the_same_bits(n, boxes, precision)
+
+
+# Partial radix rounds on swizzled rows: one step against the oracle's adjoint, to the
+# same bar.
+def test_adjoint_x_stage_96():
+    from oracle import adjoint as oadj
+    from paper_2406_01322_amd.psms import Adjoint
+    n = 96
+    prm = box.Params(n=n, re=50.0, we=1.0, ch=0.2, pe=5.0, dt=1e-3)
+    x = 2 * np.pi * np.arange(n) / n
+    z, y, x = np.meshgrid(x, x, x, indexing="ij")
+    u = np.stack([np.sin(x) * np.cos(y) * np.cos(z), -np.cos(x) * np.sin(y) * np.cos(z), 0.3 * np.cos(x + 2 * y)])
+    phi = np.cos(x) * np.sin(y - z) + 0.1 * np.random.default_rng(n).standard_normal((n, n, n))
+    J0, d0, w0, _ = oadj.gradient(u, phi, prm, 1)
+    a = Adjoint(n, prm.re, prm.we, prm.ch, prm.pe, prm.dt, precision="fp64", max_steps=1, seg_len=1)
+    J = a.forward(_dev(u), _dev(phi), 1)
+    d, w = a.backward()
+    assert abs(J - J0) <= 1e-10 * abs(J0)
+    assert np.linalg.norm(_host(d) - d0) <= 1e-10 * np.linalg.norm(d0)
+    assert abs(w - w0) <= 1e-10 * abs(w0)
+
+
+# The largest two: the derivatives along one direction of phi0 and in We against
+# central differences of J (two step sizes, extrapolated), to the 1e-6 of the adjoint
+# tests.
+@pytest.mark.parametrize("n", [192, 256])
+def test_adjoint_of_the_largest_grids(n):
+    from paper_2406_01322_amd.psms import Adjoint
+    x = 2 * np.pi * torch.arange(n, dtype=torch.float64, device="cuda") / n
+    z, y, x = torch.meshgrid(x, x, x, indexing="ij")
+    rng = np.random.default_rng(n)
+
+    def field():
+        f = torch.zeros_like(x)
+        for _ in range(6):
+            k, s = rng.integers(-3, 4, size=3), rng.uniform(0, 6)
+            f += float(rng.uniform(0.1, 0.3)) * torch.cos(float(k[0]) * x + float(k[1]) * y + float(k[2]) * z + s)
+        return f
+
+    u = torch.stack([torch.sin(x) * torch.cos(y) * torch.cos(z), -torch.cos(x) * torch.sin(y) * torch.cos(z),
+                     0.3 * torch.cos(x + 2 * y)])
+    phi, e = field(), field()
+
+    def J(s, we=1.0):
+        return Adjoint(n, 50.0, we, 0.2, 5.0, 1e-3, precision="fp64", max_steps=2, seg_len=2).forward(u, phi + s * e, 2)
+
+    def slope(f, h):
+        d = [(f(s) - f(-s)) / (2 * s) for s in (h, h / 2)]
+        return (4 * d[1] - d[0]) / 3
+
+    a = Adjoint(n, 50.0, 1.0, 0.2, 5.0, 1e-3, precision="fp64", max_steps=2, seg_len=2)
+    a.forward(u, phi, 2)
+    d, dwe = a.backward()
+    for got, want in ((float((d * e).sum()), slope(J, 1e-2)), (dwe, slope(lambda s: J(0.0, 1.0 + s), 1e-2))):
+        assert abs(got - want) <= 1e-6 * abs(want), (got, want)

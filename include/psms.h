@@ -296,8 +296,10 @@ int psms_wall_solve(const psms_wall_args* a, void* d_work, size_t bytes, void* s
  * step's H_omega, H_w, S_phi) likewise; the mean lines are [2][nc+1] complex
  * (U, V) and their history (mean S_x, S_y).  Physical fields are real double
  * [z][y][x], x_i = lx i / nx, y_j = ly j / ny.
- * Transforms and products run in FP32 for PSMS_MIXED; the state, the
- * right-hand sides and every solve are FP64.
+ * Transforms and products run in FP32 for PSMS_MIXED, and what the forward
+ * Chebyshev transform takes (combinations of the transformed products, formed in
+ * FP64) is rounded to FP32; what it gives, the state, the right-hand sides formed
+ * from both and every solve are FP64.
  * ------------------------------------------------------------------------- */
 typedef struct psms_channel_params {
   int32_t nx, ny, nc; /* nx, ny as for psms_params.n; nc in {4 6 8 12 16 24 32 48 64 96 128 256} */
@@ -385,7 +387,10 @@ int psms_batch_step(psms_batch* b, int32_t nsteps, int32_t use_graph);
  * (h_n, h_count may be NULL; otherwise they hold *h_ngroups entries). */
 int psms_batch_groups(const psms_batch* b, int32_t* h_ngroups, int32_t* h_n, int32_t* h_count);
 /* Workgroup-size variant (0, 1, 2: 64, 128, 256 threads) of each stage of each
- * group, h_variants[4 * group + stage]. */
+ * group, h_variants[4 * group + stage].  The x stage (but for FP64 boxes of N = 256)
+ * and the z stage of a group with few lines (N <= 96; at most 2048 or 4096 lines of the
+ * band in all boxes) have one shape, whatever the variant: the results never
+ * depend on it. */
 int psms_batch_set_variants(psms_batch* b, const int32_t* h_variants);
 /* Autotuner: times every variant of every stage of every group (reps
  * launches each, HIP events on the batch stream) and keeps the fastest.

@@ -900,7 +900,7 @@ int psms_cheb_helmholtz_noalloc(int32_t nc, int64_t nlines, const double* d_beta
 
 namespace {
 struct WallLayout {
-  size_t line, psi, wt, psit, wb, psib, xi, dw, xw, total;
+  size_t psi, wt, psit, wb, psib, xi, xw, total;
 };
 WallLayout wall_layout(int nc, long long nlines) {
   WallLayout L{};
@@ -912,7 +912,6 @@ WallLayout wall_layout(int nc, long long nlines) {
   L.wb = off; off += arr;
   L.psib = off; off += arr;
   L.xi = off; off += arr;
-  L.dw = off; off += arr;
   // elimination scratch of up to four problems solved in one launch
   L.xw = off; off += 4 * align256(size_t(nc + 1) * size_t(nlines) * sizeof(double));
   L.total = off;

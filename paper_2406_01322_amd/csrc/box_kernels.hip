@@ -490,11 +490,16 @@ k_xstep(const BoxDev* __restrict__ boxes, int box0, const cpx<T>* __restrict__ t
 // 16.4 -> 6.3 us; step 37.8 -> 29.0 us).  Large ones are bound by LDS traffic and
 // memory together: the fields' exchange adds to the former, and larger radices,
 // for which the registers are there now, take more away (N = 128: two
-// exchanges a transform, not three; N = 256 in FP32: one).  Steps with k_xstep and
-// now, us: FP64 64^3 48.7 -> 41.2, 96^3 96.4 -> 75.2, 128^3 127 -> 118; FP32 64^3
-// 38.6 -> 33.6, 96^3 65.8 -> 59.0, 128^3 81.4 -> 77.7, 256^3 758 -> 752; 32 boxes of
-// 64^3 FP32 336 -> 322.  With radix 4 throughout, the larger FP32 grids lost: those
-// 32 boxes 349, 128^3 82.8, 256^3 850.  Workgroups that walk over tiles, with or
+// exchanges a transform, not three; N = 256 in FP32: one).  Each product takes its own
+// wavefront's field from registers (22 LDS reads a point, not 28).  The stage with
+// k_xstep and now, us: FP64 64^3 17.2 -> 9.8, 96^3 64.7 -> 25.4, 128^3 51.8 -> 47.8,
+// 192^3 349 -> 201; FP32 32^3 13.0 -> 5.2, 64^3 13.7 -> 7.9, 96^3 32.4 -> 17.2, 128^3
+// 28.8 -> 28.9, 192^3 148 -> 114, 256^3 199 -> 189 (96 and 192 with their radix-6 plans
+// here, radix 3 and 2 there).  128^3 in FP32 is no faster and large sweeps of 32^3
+// boxes in FP32 up to 2% slower (128 boxes 177 -> 180 us a step; radix 8 x 4 would take
+// 170 there, but 0.7 us more than the 18.0 of a single box).  With radix 4 throughout, the
+// larger FP32 grids lost: steps of 128^3 81.4 -> 82.8, 256^3 758 -> 850.  Workgroups that
+// walk over tiles, with or
 // without the next tile's loads in flight, were 2 to 15% slower.
 // ---------------------------------------------------------------------------
 template <typename T, int N>
@@ -506,8 +511,9 @@ template <typename T> struct XPlanSel<T, 128> { using type = PlanT<128, 8, 8, 8,
 template <> struct XPlanSel<float, 256> { using type = PlanT<256, 16, 16, 16>; };
 template <typename T, int N>
 using XPlan = typename XPlanSel<T, N>::type;
-// FP64 rows of 256 keep the fields in registers (k_xstep): 255 us against 321 on
-// the single-phase 256 x 256 x 257 channel.
+// FP64 rows of 256 keep the fields in registers (k_xstep): 1174 us a step against
+// 1233 on the single-phase 256 x 256 x 257 channel, 1266 against 1276 on the 256^3 box.
+// (The two-phase channel alone would gain: 256 x 128 x 129 434 against 424.)
 template <typename T, int N>
 constexpr bool kXfield = !(sizeof(T) == 8 && N == 256);
 template <typename T, int N, bool CH = false, bool SP = false>
@@ -860,7 +866,7 @@ __global__ void __launch_bounds__(64 << V) k_zstep(const BoxDev* __restrict__ bo
 // L lines forward and leaves the band's modes in LDS; the modes are then updated one
 // to a thread; group f < 5 inverts the new state's field f.  One line set of a small
 // grid leaves k_zstep with a few workgroups (8 at 32^3), each a chain of 13 transforms
-// and, per thread, E modes' updates: 15 us at 32^3, where this takes 5.  Steps with
+// and, per thread, E modes' updates: 15 us at 32^3, where this takes 6.5.  Steps with
 // k_zstep and with it, us: FP64 32^3 28.0 -> 19.4, 48^3 37.6 -> 24.6, 64^3 41.0 -> 34.1,
 // 96^3 75.3 -> 71.2; FP32 32^3 25.3 -> 18.0, 64^3 33.2 -> 28.0, 96^3 58.6 -> 50.3.
 // ---------------------------------------------------------------------------

@@ -30,7 +30,9 @@ namespace {
 
 // The transforms' plans: radix 8 for lines of 128 and 256, half the threads and one
 // exchange (with its barrier) fewer (256 x 256 x 257 in FP64: products 206 -> 185 us,
-// fields 140 -> 128; five steps of 256 x 128 x 129 in MIXED 1433 -> 1424 us).
+// fields 140 -> 128; five steps of 256 x 128 x 129 in MIXED 1433 -> 1424 us).  The
+// 512-point extension (FP32, nc = 256) still runs radix 4 and 2 on 8 lines; 8 x 8 x 8 on
+// 8 lines measured 200 against 246 us for ten transforms of 14706 lines and is not built.
 template <int N>
 struct DctPlanSel {
   using type = Plan<N>;
@@ -826,8 +828,10 @@ hipError_t dct_n(const Src& in, cpx<T>* out, long long nlines, int dir, long lon
                  const cpx<T>* tw, cpx<double>* out64, int kz, hipStream_t st) {
   // Long FP64 lines take the nc-point route: half the exchange traffic (14706
   // lines, nc = 96, 128, 256: 15.8, 19.8, 44.5 us against 19.1, 23.1, 49.0).
-  // Short ones keep the even extension, with its three barriers fewer: the steps
-  // of the channels with nc = 32 and 64 take 0.95 and 0.98 of the time.  FP32
+  // Short ones keep the even extension, with its three barriers fewer, in channels of
+  // any size (us a step, extension against nc-point: 64 x 64 x 49 51 / 55, 256 x 128 x
+  // 49 162 / 171, 128 x 96 x 65 100 / 104, 256 x 128 x 65 219 / 223); alone it loses
+  // from 44000 lines of nc = 64 on (100000 lines 45 against 40 us).  FP32
   // lines keep it too: its transform is cheap against the nc-point route's FP64
   // sums (256 x 128 x 129 step: 1.45 ms against 1.55 for five), and every order
   // is formed by itself.

@@ -330,9 +330,9 @@ __device__ __forceinline__ void tau_store(const W& t, cpx<double>* __restrict__ 
 // homogeneous w solution (psi = 1 at both walls for the even parity, +-1 for the
 // odd) is a third, real right-hand side of the w chains: w'(+1) = +-w'(-1) splits
 // by parity, so each parity's correction makes its own sum n^2 w_n vanish.
-// Measured at 7310 lines x 129: 46 us (90 MB read and written; bound by the chains'
-// latency at one workgroup of 8 wavefronts per compute unit), where one lane per
-// chain took three launches of 55 us and 174 us for the influence sums.
+// Measured at 7310 lines x 129: 47 us (90 MB read and written; bound by the chains'
+// latency at one workgroup of 8 wavefronts, two a SIMD, per compute unit), where one
+// lane per chain took three launches of 55 us and 174 us for the influence sums.
 // ---------------------------------------------------------------------------
 template <int NC>
 __global__ void __launch_bounds__(64 * tau_pieces(NC)) k_wall_tau(WallTauArgs a) {
@@ -406,12 +406,16 @@ __global__ void __launch_bounds__(64 * tau_pieces(NC)) k_wall_tau(WallTauArgs a)
 //
 // Bytes per step at 256 x 128 x 129: 250 MB (state and history read and written,
 // six term arrays up to n = kz, wh), where separate derivative, assembly and solve
-// passes moved 900 MB.  Measured there: 93 us, where the derivative, assembly and solve
-// launches took 193 us; 256 x 256 x 257 single phase 245 us, where they took 935 us.
+// passes moved 900 MB.  Measured there: 94 us, where the derivative, assembly and solve
+// launches took 211 us; 256 x 256 x 257 single phase 264 us, where they took 935 us.
 // It is bound by the latency of its chains of FP64 operations, scans and barriers
-// (a workgroup takes 20 to 30 us and a compute unit holds one, 188 VGPRs): held to
-// 128 VGPRs it spills and takes 30% longer, 16 pieces of 5 terms take 6% longer,
-// and unrolled scans over the pieces change nothing.
+// (a workgroup takes 20 to 30 us and a compute unit holds one, two wavefronts a SIMD,
+// 188 VGPRs): held to 128 VGPRs it spills and takes 30% longer, 16 pieces of 5 terms take
+// 6% longer, and unrolled scans over the pieces change nothing.  The chains of nc = 256
+// have 17 terms a piece: 256 VGPRs and 80 more in scratch.
+// With different walls (BOTH) the workgroup's 1024 threads hold it to 128 VGPRs: 23, 61
+// and 433 are spilled at nc = 96, 128 and 256.  It takes 31 us at 128 x 96 x 65, 71 at
+// 128 x 96 x 129 and 191 at 96 x 64 x 257, where the former launches took 120, 259 and 433.
 // ---------------------------------------------------------------------------
 
 // (D f)_n = s_n sum_{j >= n, j = n mod 2} 2 (j + 1) f_{j+1} (s_0 = 1/2): the piece's
@@ -625,7 +629,6 @@ __global__ void __launch_bounds__((BOTH ? 128 : 64) * tau_pieces(NC)) k_chan_tau
   {
     double hp[LEN][2];
     tau_load<0>(t, hist, ns, lc, NC, hp);
-    
 #pragma unroll
     for (int k = 0; k < LEN; ++k) {
       if (valid && t.in(k)) (hist + (long long)t.n(k) * ns)[lc] = cpx<double>{x[k][0], x[k][1]};

@@ -404,8 +404,9 @@ __global__ void __launch_bounds__(64 * tau_pieces(NC)) k_wall_tau(WallTauArgs a)
 // what comes in.  A parity's chain reads B, Q of the other parity and A, P of its
 // own, so every array is read once.
 //
-// Bytes per step at 256 x 128 x 129: 250 MB (state and history read and written,
-// six term arrays up to n = kz, wh), where separate derivative, assembly and solve
+// Bytes per step at 256 x 128 x 129: 309 MB counted, 189 read (state and history, phi
+// twice, six term arrays up to n = kz, wh) and 121 written (state, history, D w, D
+// phi), 60 us at the rate of a copy, where separate derivative, assembly and solve
 // passes moved 900 MB.  Measured there: 94 us, where the derivative, assembly and solve
 // launches took 211 us; 256 x 256 x 257 single phase 264 us, where they took 935 us.
 // It is bound by the latency of its chains of FP64 operations, scans and barriers

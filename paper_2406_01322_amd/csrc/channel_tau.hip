@@ -27,16 +27,14 @@ namespace psms {
 
 namespace {
 
-// Pieces of a chain: the smallest power of two with at most 7 terms a piece, up to 8.
-// More leave wavefronts without terms, which costs nothing while a launch is a few
-// workgroups and everything once it fills the chip (60000 lines: nc = 4 22 us where 8
-// pieces took 101, nc = 16 43 against 123; 15000 lines, nc = 48 37 against 55; 256 x
-// 128 x 49 channel step, FP64 161 against 170).
-constexpr int tau_pieces(int nc) {
-  int p = 1;
-  while (p < 8 && nc / 2 + 1 > 7 * p) p *= 2;
-  return p;
-}
+// Pieces of a chain: 8, and one up to nc = 16 (9 terms, what a piece has at nc = 128).
+// Pieces of one or two terms leave wavefronts with nothing to do, which costs little
+// while a launch is a few workgroups and everything once it fills the chip (five wall
+// solves of 60000 lines, 8 pieces and one: nc = 4 509 and 122 us, nc = 16 617 and 178; a
+// 256 x 128 x 17 channel step 93 and 84), and one piece has the smaller error (omega at
+// nc = 16, beta 3e6: 5.3e-14 and 3.6e-14).  Two or four pieces for nc = 24 to 48 are faster
+// as well (60000 lines, nc = 24: 670 and 289), but their error is larger (1.3e-14 and 2.6e-14).
+constexpr int tau_pieces(int nc) { return nc <= 16 ? 1 : 8; }
 constexpr int tau_len(int nc) { return (nc / 2 + 1 + tau_pieces(nc) - 1) / tau_pieces(nc); }
 
 // The rows (tau_rows.hpp) of chain length NC at every piece's slots, by parity:

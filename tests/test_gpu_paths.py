@@ -425,8 +425,8 @@ def test_restart_takes_the_same_bits(nc, walls, single, precision):
     assert all(torch.equal(x, y) for x, y in zip(a.get_state(with_history=True), b.get_state(with_history=True)))
 
 
-# Chains in one piece (up to nc = 12, 7 terms), two (16, 24) and four (32, 48): line
-# counts around a workgroup's 64, alone and in a step whose walls couple the parities.
+# Chains in one piece (up to nc = 16) and just beyond: line counts around a workgroup's
+# 64, alone and in a step whose walls couple the parities.
 @pytest.mark.parametrize("nc,nl", [(4, 64), (12, 63), (16, 65), (24, 128), (32, 63), (48, 130), (64, 1)])
 def test_wall_solve_piece_counts(nc, nl):
     test_pieced_wall_solve_sizes(nc, nl)
